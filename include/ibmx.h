@@ -194,7 +194,7 @@ IBMX_API ibmx_status ibmx_plan_set_markers(ibmx_plan plan, const double *body_of
 
 /* Flags of ibmx_plan_reserve. */
 #define IBMX_RESERVE_BACKWARD 1   /* replay workspace of ibmx_forcing_backward  */
-#define IBMX_RESERVE_FLUID 2      /* FFT / elimination workspace of ibmx_project
+#define IBMX_RESERVE_FLUID 2      /* FFT workspace of ibmx_project
                                      and ibmx_fluid_helmholtz                   */
 
 /*
@@ -208,8 +208,7 @@ IBMX_API ibmx_status ibmx_plan_set_markers(ibmx_plan plan, const double *body_of
  *   IBMX_RESERVE_BACKWARD    ibmx_forcing_backward (the replay grid T[3][nodes]
  *                            and T4[n_iter][3][nm] of per-pass data);
  *   IBMX_RESERVE_FLUID       ibmx_project and ibmx_fluid_helmholtz (an FP64
- *                            real grid, the FP64 half spectrum, with walls in z
- *                            an FP64 elimination grid, twiddle tables);
+ *                            real grid, the FP64 half spectrum, twiddle tables);
  *                            EUNSUPPORTED on grids the solves do not take.
  * Workspace only grows; a call whose needs exceed the reservation returns
  * ESTATE.  Synchronises the plan's stream.  Growing it moves the workspace,
@@ -522,12 +521,11 @@ IBMX_API ibmx_status ibmx_particle_substeps(ibmx_plan plan, double dt_total, int
  * uf     T[3][nz][ny][nx], out: normal velocity on the +x, +y, +z face of
  *        each cell (0 on a wall face).
  * P      T[nz][ny][nx], in/out.  phi: T[nz][ny][nx] or NULL, out.
- * The solve is direct and FP64: FFTs along x and y (and z when periodic),
- * across walls in z a tridiagonal elimination per Fourier mode.  Needs
+ * The solve is direct and FP64: FFTs along x and y and, per Fourier mode, the
+ * three-point system along z (between walls or periodic).  Needs
  * periodic x and y with power-of-two sizes up to 1024 (and the same for z
  * when periodic), else EUNSUPPORTED.  The solver workspace (an FP64 real
- * grid, the FP64 complex half spectrum of nx/2 + 1 modes per row, with walls
- * in z an FP64 grid of elimination coefficients of the same shape, and one
+ * grid, the FP64 complex half spectrum of nx/2 + 1 modes per row and one
  * twiddle table per axis) comes from ibmx_plan_reserve with
  * IBMX_RESERVE_FLUID, else ESTATE.
  */
@@ -563,9 +561,8 @@ IBMX_API ibmx_status ibmx_fluid_predictor(ibmx_plan plan, const void *u, void *u
  * velocity (from ibmx_fluid_predictor), fbar the mean IBM force (device
  * double[3], e.g. from ibmx_grid_mean of f_tot, for triply periodic cases;
  * NULL for 0) and theta 0 (pressure projection) or 1 (pressure correction).
- * u is overwritten by u*.  The solve is FP64: FFTs along x and y (and z when
- * periodic), across walls in z a tridiagonal elimination per Fourier mode
- * with velocity 0 on the wall faces.  Same grid conditions and workspace as
+ * u is overwritten by u*.  The solve is FP64: FFTs along x and y and, per
+ * Fourier mode, the three-point system along z (velocity 0 on wall faces).  Same grid conditions and workspace as
  * ibmx_project (ESTATE without it).
  */
 IBMX_API ibmx_status ibmx_fluid_helmholtz(ibmx_plan plan, void *u, const void *lapnu, const void *P,

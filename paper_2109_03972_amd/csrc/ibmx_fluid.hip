@@ -6,9 +6,9 @@
 // Both implicit systems, (I - beta L) u* = r per velocity component and the
 // compact Poisson equation L phi = div(u_f*) / c, are solved directly in
 // FP64 for a real right-hand side: a real-to-complex FFT along x (the
-// nx/2 + 1 modes of each row), complex FFTs along y (and z when periodic,
-// then a division by the eigenvalues), or per (kx, ky) mode a tridiagonal
-// elimination across the walls in z.  The half spectrum is stored with y
+// nx/2 + 1 modes of each row), complex FFTs along y, and per (kx, ky) mode the
+// three-point system along z, periodic or between walls, as two recursive
+// filters in one pass over the spectrum (k_zsolve).  The half spectrum is stored with y
 // fastest, mode (kx, y, z) at (z (nx/2 + 1) + kx) ny + y, so that the y
 // passes read whole contiguous lines and the x passes, taking 8 or more
 // consecutive rows per workgroup, read and write runs of consecutive y.  FFTs
@@ -478,9 +478,290 @@ __device__ __forceinline__ double lam(int m, int n, double h)
     return (2.0 * cospi(2.0 * m / (double)n) - 2.0) / (h * h);
 }
 
+// ---------------------------------------------------------------------------
+// Solve along z of one (kx, ky) mode: a x_{k-1} + q x_k + a x_{k+1} = d_k with
+// a = s1/h^2, q = e - 2a, e = s0 + s1 lambda_xy, closed periodically, by an
+// even reflection at the walls (zero gradient: the pressure) or by an odd one
+// (ghost -x: the velocity).  With e and a of opposite sign (e / a < 0) the
+// operator factors into (q / (1 + r^2)) (1 - r E^-)(1 - r E^+), r + 1/r =
+// -q/a, 0 <= r < 1, E^-+ the shifts along z, so the solution is
+//   y_k = d_k + r y_{k-1}          up,
+//   x_k = s y_k + r x_{k+1}        down, s = (1 + r^2)/q,
+// on the sequence extended by the closure (period nz, or 2 nz with walls):
+// the extension only sets the values y_{-1} and x_{nz},
+//   periodic  y_{-1} = F / (1 - r^nz),       x_nz = G / (1 - r^nz),
+//   walls     y_{-1} = (+-B + r^nz F)/(1 - r^2nz),  x_nz = +- s y_{nz-1}/(1 -+ r),
+// F, G the filters' ends from zero (F = sum r^(nz-1-k) d_k, G = sum r^k s y_k)
+// and B = sum r^k d_k.  All r enter as 1 - r = dl, found without
+// cancellation: low modes have r close to 1, and y -> y - dl y keeps their
+// rounding at the level of the elimination's.
+//
+// A workgroup holds 8 neighbouring modes (128 B runs in memory) and their
+// whole columns in registers, C rows per thread, 8 chunks of rows per wave;
+// the filters run within the chunks, the chunk ends are combined by a wave
+// scan and over the waves through LDS.  Rows are padded in front (chunk 0).
+// What bounds it is memory: 16 B read and 16 B written per mode value, once,
+// where the elimination and substitution read and write it twice (and a
+// periodic z takes a forward FFT, a division and an inverse FFT: three times).
+// On 512^3 with walls 483 us a solve (2.16 GB, 4.5 TB/s, the copy rate)
+// against 946; on 128^3 periodic 17 us against 53.
+// ---------------------------------------------------------------------------
+constexpr int kZModes = 8;                            // modes per workgroup
+constexpr int kZChunks = IBMX_WAVE / kZModes;         // row chunks per wave
+constexpr int kZMaxWaves = 16;
+enum { kZPeriodic = 0, kZNeumann = 1, kZDirichlet = -1 };
+
+__device__ __forceinline__ double2 operator+(double2 a, double2 b)
+{
+    return make_double2(a.x + b.x, a.y + b.y);
+}
+__device__ __forceinline__ double2 operator*(double a, double2 b)
+{
+    return make_double2(a * b.x, a * b.y);
+}
+// d + r v with r = 1 - dl
+__device__ __forceinline__ double2 z_step(double2 d, double2 v, double dl)
+{
+    return make_double2(fma(-dl, v.x, v.x + d.x), fma(-dl, v.y, v.y + d.y));
+}
+// r^m r^n = (1 - a)(1 - b) -> 1 - that
+__device__ __forceinline__ double z_mul(double a, double b) { return a + b - a * b; }
+// 1 - (1 - dl)^n
+__device__ __forceinline__ double z_pow(double dl, int n)
+{
+    double r = 0.0;
+    for (; n > 0; n >>= 1) {
+        if (n & 1)
+            r = z_mul(r, dl);
+        dl = dl * (2.0 - dl);
+    }
+    return r;
+}
+__device__ __forceinline__ double2 z_shfl_up(double2 v, int d)
+{
+    return make_double2(__shfl_up(v.x, d, IBMX_WAVE), __shfl_up(v.y, d, IBMX_WAVE));
+}
+__device__ __forceinline__ double2 z_shfl_down(double2 v, int d)
+{
+    return make_double2(__shfl_down(v.x, d, IBMX_WAVE), __shfl_down(v.y, d, IBMX_WAVE));
+}
+// sum over the chunks of a wave, in every lane of the mode
+__device__ __forceinline__ double2 z_wave_sum(double2 v)
+{
+#pragma unroll
+    for (int d = kZModes; d < IBMX_WAVE; d <<= 1) {
+        v.x += __shfl_xor(v.x, d, IBMX_WAVE);
+        v.y += __shfl_xor(v.y, d, IBMX_WAVE);
+    }
+    return v;
+}
+
+// KIND: the closure; the system with s0 = 0 and a zero-gradient or periodic
+// closure is singular in the (0, 0) mode, whose solution of zero mean is the
+// double prefix sum (r = 1) less its mean.
+template <int C, int KIND>
+__global__ __launch_bounds__(C == 16 ? 1024 : 256) void k_zsolve(
+    FluidC F, int logny, double s0, double s1, double2 *__restrict__ Z)
+{
+    __shared__ double2 w_end[kZMaxWaves][kZModes], w_sum[kZMaxWaves][kZModes],
+        w_red[kZMaxWaves][kZModes];
+    const int lane = threadIdx.x & (IBMX_WAVE - 1), wv = threadIdx.x / IBMX_WAVE;
+    const int nw = blockDim.x / IBMX_WAVE;
+    const int mode = lane & (kZModes - 1), ci = lane / kZModes;
+    const int nz = F.n[2], nxy = (F.n[0] / 2 + 1) << logny;
+    const int col = blockIdx.x * kZModes + mode;
+    const int pad = nw * kZChunks * C - nz;
+    const int k0 = (wv * kZChunks + ci) * C - pad;     // row of the thread's first slot
+    const int ks = k0 > 0 ? k0 : 0;                    // and of its first true row
+    double2 v[C];
+#pragma unroll
+    for (int r = 0; r < C; ++r)
+        v[r] = col < nxy && k0 + r >= 0 ? Z[(size_t)(k0 + r) * nxy + col] : make_double2(0.0, 0.0);
+    const int i = col >> logny, j = col & ((1 << logny) - 1);
+    const double ih2 = 1.0 / (F.h * F.h), a = s1 * ih2;
+    const double e = s0 + s1 * (lam(i, F.n[0], F.h) + lam(j, F.n[1], F.h));
+    const double q = e - 2.0 * a;
+    // eps = r + 1/r - 2, dl = 1 - r = 2 eps / (eps + sqrt(eps (eps + 4)))
+    const double eps = -e / a;
+    double dl = a == 0.0 ? 1.0 : 2.0 * eps / (eps + sqrt(eps) * sqrt(eps + 4.0));
+    double s = (1.0 + (1.0 - dl) * (1.0 - dl)) / q;
+    const bool singular_block = KIND != kZDirichlet && s0 == 0.0 && blockIdx.x == 0;
+    const bool singular = singular_block && col == 0;
+    if (singular) {
+        dl = 0.0;
+        s = -1.0 / a;
+    }
+    // the mean over the rows of one value per thread and row (for the
+    // singular mode; every thread of the block calls it)
+    auto row_mean = [&]() {
+        double2 t = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int r = 0; r < C; ++r)
+            if (k0 + r >= 0)
+                t = t + v[r];
+        t = z_wave_sum(t);
+        __syncthreads();
+        if (ci == 0)
+            w_red[wv][mode] = t;
+        __syncthreads();
+        t = w_red[0][mode];
+        for (int w = 1; w < nw; ++w)
+            t = t + w_red[w][mode];
+        return (1.0 / nz) * t;
+    };
+    auto take_mean = [&]() {
+        const double2 m = row_mean();
+        if (singular)
+#pragma unroll
+            for (int r = 0; r < C; ++r)
+                v[r] = v[r] + (-1.0) * m;
+    };
+    if (KIND == kZPeriodic && singular_block)
+        take_mean();
+    // powers of r over a chunk, 2, 4 and 8 chunks, and over the whole column
+    double dC = dl;
+#pragma unroll
+    for (int c = 1; c < C; c <<= 1)
+        dC = dC * (2.0 - dC);
+    const double d2 = dC * (2.0 - dC), d4 = d2 * (2.0 - d2), d8 = d4 * (2.0 - d4);
+    const double dn = z_pow(dl, nz), dks = z_pow(dl, ks);
+    auto chunks_pow = [&](int n) {   // n < 8 chunks
+        double p = (n & 1) ? dC : 0.0;
+        if (n & 2)
+            p = z_mul(p, d2);
+        if (n & 4)
+            p = z_mul(p, d4);
+        return p;
+    };
+    // up: the chunk's filter from zero, its end, and with walls the chunk's
+    // share of B
+    if (KIND != kZPeriodic) {
+        double2 b = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int r = C - 1; r >= 0; --r)
+            if (k0 + r >= 0)
+                b = z_step(v[r], b, dl);
+        b = z_wave_sum((1.0 - dks) * b);
+        if (ci == 0)
+            w_sum[wv][mode] = b;
+    }
+#pragma unroll
+    for (int r = 1; r < C; ++r)
+        v[r] = z_step(v[r], v[r - 1], dl);
+    double2 E = v[C - 1];
+    {
+        double2 t = z_shfl_up(E, kZModes);
+        if (ci >= 1)
+            E = z_step(E, t, dC);
+        t = z_shfl_up(E, 2 * kZModes);
+        if (ci >= 2)
+            E = z_step(E, t, d2);
+        t = z_shfl_up(E, 4 * kZModes);
+        if (ci >= 4)
+            E = z_step(E, t, d4);
+    }
+    if (ci == kZChunks - 1)
+        w_end[wv][mode] = E;
+    __syncthreads();
+    double2 cw = make_double2(0.0, 0.0), Fe = cw, B = cw;
+    for (int w = 0; w < nw; ++w) {
+        if (w == wv)
+            cw = Fe;
+        Fe = z_step(w_end[w][mode], Fe, d8);
+        if (KIND != kZPeriodic)
+            B = B + w_sum[w][mode];
+    }
+    // y before row 0, and before the chunk
+    double2 Y0 = make_double2(0.0, 0.0), X0 = Y0;
+    if (!singular) {
+        if (KIND == kZPeriodic) {
+            Y0 = (1.0 / dn) * Fe;
+        } else {
+            Y0 = (1.0 / (dn * (2.0 - dn))) * ((double)KIND * B + (1.0 - dn) * Fe);
+            const double2 ye = Fe + (1.0 - dn) * Y0;
+            X0 = ((double)KIND * s / (KIND == kZNeumann ? dl : 2.0 - dl)) * ye;
+        }
+    }
+    {
+        double2 c = z_shfl_up(E, kZModes);
+        if (ci == 0)
+            c = make_double2(0.0, 0.0);
+        c = c + (1.0 - chunks_pow(ci)) * cw + (1.0 - dks) * Y0;
+#pragma unroll
+        for (int r = 0; r < C; ++r)
+            if (k0 + r >= 0) {
+                c = make_double2(fma(-dl, c.x, c.x), fma(-dl, c.y, c.y));
+                v[r] = v[r] + c;
+            }
+    }
+    if (singular_block) {
+        if (KIND == kZPeriodic) {
+            take_mean();
+        } else if (singular && k0 + C == nz) {
+            v[C - 1] = make_double2(0.0, 0.0);   // the top value is pinned to 0
+        }
+    }
+    // down: the same from the top
+    {
+        double2 g = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int r = C - 1; r >= 0; --r)
+            if (k0 + r >= 0) {
+                g = z_step(s * v[r], g, dl);
+                v[r] = g;
+            }
+        if (KIND == kZPeriodic) {
+            const double2 t = z_wave_sum((1.0 - dks) * g);
+            if (ci == 0)
+                w_sum[wv][mode] = t;
+        }
+        E = g;
+        double2 t = z_shfl_down(E, kZModes);
+        if (ci < kZChunks - 1)
+            E = z_step(E, t, dC);
+        t = z_shfl_down(E, 2 * kZModes);
+        if (ci < kZChunks - 2)
+            E = z_step(E, t, d2);
+        t = z_shfl_down(E, 4 * kZModes);
+        if (ci < kZChunks - 4)
+            E = z_step(E, t, d4);
+    }
+    __syncthreads();
+    if (ci == 0)
+        w_end[wv][mode] = E;
+    __syncthreads();
+    if (KIND == kZPeriodic && !singular) {
+        double2 G = w_sum[0][mode];
+        for (int w = 1; w < nw; ++w)
+            G = G + w_sum[w][mode];
+        X0 = (1.0 / dn) * G;
+    }
+    for (int w = nw - 1; w > wv; --w)
+        X0 = z_step(w_end[w][mode], X0, d8);
+    {
+        double2 c = z_shfl_down(E, kZModes);
+        if (ci == kZChunks - 1)
+            c = make_double2(0.0, 0.0);
+        c = c + (1.0 - chunks_pow(kZChunks - 1 - ci)) * X0;
+#pragma unroll
+        for (int r = C - 1; r >= 0; --r) {
+            c = make_double2(fma(-dl, c.x, c.x), fma(-dl, c.y, c.y));
+            v[r] = v[r] + c;
+        }
+    }
+    if (singular_block)
+        take_mean();
+    if (col >= nxy)
+        return;
+#pragma unroll
+    for (int r = 0; r < C; ++r)
+        if (k0 + r >= 0)
+            Z[(size_t)(k0 + r) * nxy + col] = v[r];
+}
+
 // triply periodic: mode by mode x = d / (s0 + s1 lambda) over the modes
 // kx = 0 .. nx/2 held for real fields (y fastest); with s0 = 0 the mean mode
-// is 0
+// is 0 (after a forward FFT along z; where k_zsolve does not apply)
 __global__ __launch_bounds__(256) void k_divide(FluidC F, double s0, double s1,
                                                 double2 *__restrict__ Z)
 {
@@ -496,7 +777,8 @@ __global__ __launch_bounds__(256) void k_divide(FluidC F, double s0, double s1,
     }
 }
 
-// walls in z: per (kx, ky) mode (kx = 0 .. nx/2; modes y-fastest) the system
+// walls in z, where k_zsolve does not apply: per (kx, ky) mode (kx = 0 ..
+// nx/2; modes y-fastest) the system
 // s0 x + s1 (D_z + lambda_xy) x = rhs, D_z the second difference
 // (1/h^2)(x_{k+1} - 2 x_k + x_{k-1}) closed
 // at the walls by a zero gradient (Neumann, the pressure) or by the ghost
@@ -850,32 +1132,79 @@ FluidC fluid_constants(const ibmx_plan p, double theta)
     return F;
 }
 
+// Whether k_zsolve takes the system s0 + s1 L along z: its filters need e =
+// s0 + s1 lambda_xy and s1 of opposite sign in every mode (s1 < 0 with s0 > 0,
+// or the pressure's s0 = 0, s1 > 0; a negative viscous number or step has a
+// root on the unit circle instead), a root not so close to 1 that a reflected
+// wall solution cancels (the loss is about sqrt(|s1| / s0) / h roundings: 30 at
+// the line drawn, 1 at the viscous numbers of a run, about 0.01) and the
+// column within a workgroup's registers (2048 rows).  Between walls columns of
+// fewer than 16 rows would leave over half of the row slots (32 at least)
+// empty; the elimination takes them, and whatever else is left (with a
+// periodic z an FFT and a division).
+bool zsolve_ok(const FluidC &F, double s0, double s1)
+{
+    const bool pressure = s0 == 0.0 && s1 > 0.0;
+    const bool viscous = s0 > 0.0 && s1 <= 0.0 && -s1 <= 1000.0 * s0 * F.h * F.h;
+    return (pressure || viscous) && F.n[2] <= 16 * kZChunks * kZMaxWaves &&
+           (F.periodic[2] || F.n[2] >= 16);
+}
+
+template <int C>
+void launch_zsolve_c(ibmx_plan p, const FluidC &F, double s0, double s1, int dirichlet,
+                     hipStream_t s)
+{
+    int logny = 0;
+    while ((1 << logny) < F.n[1])
+        ++logny;
+    const int nxy = (F.n[0] / 2 + 1) * F.n[1];
+    const dim3 grid((nxy + kZModes - 1) / kZModes);
+    const dim3 block(IBMX_WAVE * ((F.n[2] + kZChunks * C - 1) / (kZChunks * C)));
+    if (F.periodic[2])
+        hipLaunchKernelGGL((k_zsolve<C, kZPeriodic>), grid, block, 0, s, F, logny, s0, s1, p->fl_z);
+    else if (dirichlet)
+        hipLaunchKernelGGL((k_zsolve<C, kZDirichlet>), grid, block, 0, s, F, logny, s0, s1,
+                           p->fl_z);
+    else
+        hipLaunchKernelGGL((k_zsolve<C, kZNeumann>), grid, block, 0, s, F, logny, s0, s1, p->fl_z);
+}
+
+// rows per thread: at most four waves per workgroup while the column allows
+// it (short columns keep few rows per thread and many waves in flight)
+void launch_zsolve(ibmx_plan p, const FluidC &F, double s0, double s1, int dirichlet,
+                   hipStream_t s)
+{
+    if (F.n[2] <= 4 * 4 * kZChunks)
+        launch_zsolve_c<4>(p, F, s0, s1, dirichlet, s);
+    else if (F.n[2] <= 8 * 4 * kZChunks)
+        launch_zsolve_c<8>(p, F, s0, s1, dirichlet, s);
+    else
+        launch_zsolve_c<16>(p, F, s0, s1, dirichlet, s);
+}
+
 // the half spectrum in fl_z (after rows_forward) -> that of the solution of
-// (s0 + s1 L) x = r (before rows_inverse); the passes are unnormalised, the
-// result comes back multiplied by 1 / spectrum_scale
-void solve_spectrum(ibmx_plan p, const FluidC &F, double s0, double s1, int dirichlet,
+// (s0 + s1 L) x = r (before rows_inverse); the FFTs are unnormalised, the
+// factor that makes up for them is returned
+double solve_spectrum(ibmx_plan p, const FluidC &F, double s0, double s1, int dirichlet,
                     hipStream_t s)
 {
     const int mx = F.n[0] / 2 + 1;
+    double scale = 1.0 / ((double)(F.n[0] / 2) * F.n[1]);
     fft_axis<false>(p, F, 1, s);
-    if (F.periodic[2]) {
+    if (zsolve_ok(F, s0, s1)) {
+        launch_zsolve(p, F, s0, s1, dirichlet, s);
+    } else if (F.periodic[2]) {
         fft_axis<false>(p, F, 2, s);
         hipLaunchKernelGGL(k_divide, dim3((F.n[1] + 255) / 256, mx, F.n[2]), dim3(256), 0, s, F,
                            s0, s1, p->fl_z);
         fft_axis<true>(p, F, 2, s);
+        scale /= F.n[2];
     } else {
         const int nxy = mx * F.n[1];
         hipLaunchKernelGGL(k_tridiag, dim3((nxy + 255) / 256), dim3(256), 0, s, F, s0, s1,
-                           dirichlet, p->fl_z, p->fl_cp);
+                           dirichlet, p->fl_z, p->fl_r);
     }
     fft_axis<true>(p, F, 1, s);
-}
-
-double spectrum_scale(const FluidC &F)
-{
-    double scale = 1.0 / ((double)(F.n[0] / 2) * F.n[1]);
-    if (F.periodic[2])
-        scale /= F.n[2];
     return scale;
 }
 
@@ -902,9 +1231,9 @@ ibmx_status run_project(ibmx_plan p, T *u, T *uf, T *P, T *phi, double theta)
     ProfScope ps(p, IBMX_K_OTHER);
     IBMX_STENCIL_LAUNCH(k_face_div, T, F, s, (const T *)u, uf, p->fl_r);
     rows_forward(p, F, RealIn{p->fl_r}, s);
-    solve_spectrum(p, F, 0.0, 1.0, 0, s);
+    const double scale = solve_spectrum(p, F, 0.0, 1.0, 0, s);
     rows_inverse(p, F, RealOut{p->fl_r}, s);
-    IBMX_STENCIL_LAUNCH(k_correct, T, F, s, (const double *)p->fl_r, spectrum_scale(F), u, uf, P,
+    IBMX_STENCIL_LAUNCH(k_correct, T, F, s, (const double *)p->fl_r, scale, u, uf, P,
                         phi);
     return ibmx_launch_check();
 }
@@ -948,8 +1277,8 @@ ibmx_status run_helmholtz(ibmx_plan p, T *u, const T *lapnu, const T *P, const d
             in.fb = 0.0;
             rows_forward(p, F, in, s);
         }
-        solve_spectrum(p, F, 1.0, -alpha * dt * F.nu, 1, s);
-        rows_inverse(p, F, ScaledOut<T>{u + (size_t)b * N, spectrum_scale(F)}, s);
+        const double scale = solve_spectrum(p, F, 1.0, -alpha * dt * F.nu, 1, s);
+        rows_inverse(p, F, ScaledOut<T>{u + (size_t)b * N, scale}, s);
     }
     return ibmx_launch_check();
 }
@@ -962,13 +1291,12 @@ bool solver_grid_ok(const ibmx_grid &g)
 
 }  // namespace
 
-// workspace: the real right-hand side / solution grid, the half spectrum
-// (nx/2 + 1 modes along x), the elimination scratch (walls in z) and one
-// twiddle table per axis
+// workspace: the real right-hand side / solution grid (free between the x
+// passes, when the elimination keeps its coefficients there), the half
+// spectrum (nx/2 + 1 modes along x) and one twiddle table per axis
 bool ibmx_fluid_ready(ibmx_plan p)
 {
-    return p->fl_r && p->fl_z && (p->grid.periodic[2] || p->fl_cp) && p->fl_tw[0] &&
-           p->fl_tw[1] && p->fl_tw[2];
+    return p->fl_r && p->fl_z && p->fl_tw[0] && p->fl_tw[1] && p->fl_tw[2];
 }
 
 bool ibmx_fluid_grid_ok(ibmx_plan p) { return solver_grid_ok(p->grid); }
@@ -983,11 +1311,6 @@ ibmx_status ibmx_fluid_reserve(ibmx_plan p)
     }
     if (!p->fl_z && hipMalloc((void **)&p->fl_z, sizeof(double2) * M) != hipSuccess) {
         p->fl_z = nullptr;
-        return IBMX_ENOMEM;
-    }
-    if (!p->grid.periodic[2] && !p->fl_cp &&
-        hipMalloc((void **)&p->fl_cp, sizeof(double) * M) != hipSuccess) {
-        p->fl_cp = nullptr;
         return IBMX_ENOMEM;
     }
     for (int a = 0; a < 3; ++a) {

@@ -103,7 +103,6 @@ struct ibmx_plan_s {
     // fluid-solve workspace (first ibmx_project / ibmx_fluid_helmholtz call)
     double *fl_r;         // real right-hand side / solution [nodes]
     double2 *fl_z;        // half spectrum [nz][ny][nx/2 + 1]
-    double *fl_cp;        // elimination scratch [nz][ny][nx/2 + 1]
     double2 *fl_tw[3];
 
     // last-call statistics

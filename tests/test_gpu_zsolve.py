@@ -1,0 +1,73 @@
+"""The solve along z of the fluid steps at the column lengths where its
+split changes (rows per thread, waves per column, front padding), with walls
+and periodic, and the systems that keep the elimination or the FFT along z (a
+negative or very large viscous number, columns over 2048 rows), against the
+FP64 oracle.
+
+Tolerance 1e-12 in FP64: the filters lose about 1/sqrt(eps) roundings in a
+mode, eps its distance from the singular system (3.8e-5 at 1024 points,
+4e-2 here), below the elimination's own 1e-13."""
+import numpy as np
+import pytest
+
+from oracle import fluid_stage as fs
+from oracle import projection as pj
+from paper_2109_03972_amd import ibmx
+from tests._util import rel_err, require_gpu
+from tests.test_gpu_fluid import _case, _run
+
+pytestmark = pytest.mark.gpu
+
+WALLS = [15, 16, 31, 33, 127, 128, 129, 256, 257, 513]
+
+
+@pytest.mark.parametrize("nz,wall", [(n, 1) for n in WALLS] +
+                         [(n, 0) for n in (8, 32, 128, 256, 512, 1024)])
+def test_projection_columns(nz, wall):
+    n, per = (8, 8, nz), (1, 1, 0 if wall else 1)
+    case = _case(n, per, seed=nz)
+    rng = np.random.default_rng(nz)
+    u0, P0 = rng.normal(0.0, 1.0, (3, nz, 8, 8)), rng.normal(0.0, 1.0, (nz, 8, 8))
+    prm = case.params
+    ref = pj.project(u0, P0, case.h, prm["c"], prm["nu_f"], 0.0, per)
+    got = _run(case, "f64", u0, P0, 0.0)
+    for k in ("u", "uf", "P", "phi"):
+        assert rel_err(got[k], ref[k]) <= 1e-12, k
+
+
+@pytest.mark.parametrize("nz", [1025, 2048, 2049])
+def test_projection_long_columns(nz):
+    """Columns at the end of the range, where the oracle's dense solves take
+    too long: the projected faces are divergence-free to the rounding of phi
+    (each of the Laplacian's 12 weights 1/h^2, 32 roundings)."""
+    n, per = (8, 8, nz), (1, 1, 0)
+    case = _case(n, per, seed=nz)
+    rng = np.random.default_rng(nz)
+    u0, P0 = rng.normal(0.0, 1.0, (3, nz, 8, 8)), rng.normal(0.0, 1.0, (nz, 8, 8))
+    got = _run(case, "f64", u0, P0, 0.0)
+    tol = 32 * 12 * np.finfo(float).eps * np.abs(got["phi"]).max() * case.params["c"] / case.h ** 3
+    assert np.abs(pj.face_div(got["uf"], case.h, per)).max() <= tol
+    assert abs(got["phi"].mean()) <= 1e-12 * np.abs(got["phi"]).max()
+
+
+@pytest.mark.parametrize("nz,wall", [(n, 1) for n in WALLS] + [(n, 0) for n in (8, 64, 256)])
+@pytest.mark.parametrize("nu", [0.3, 0.0, -0.1, 1.0e3, 1.0e5])
+def test_viscous_columns(nz, wall, nu):
+    import torch
+    dev = require_gpu()
+    n, per = (8, 8, nz), (1, 1, 0 if wall else 1)
+    case = _case(n, per, seed=3)
+    alpha, dt = 1.0 / 15.0, 0.4
+    case.params = dict(case.params, c=2.0 * alpha * dt, nu_f=nu)
+    rng = np.random.default_rng(nz)
+    shape = (3, nz, n[1], 8)
+    u0, lap = rng.normal(size=shape), rng.normal(size=shape)
+    P = rng.normal(size=shape[1:])
+    ref = fs.helmholtz(u0, lap, P, None, case.h, nu, alpha, 0.0, dt, per)
+    plan = ibmx.Plan.from_case(case, "f64")
+    u = torch.as_tensor(u0, device=dev).contiguous()
+    plan.fluid_helmholtz(u, torch.as_tensor(lap, device=dev), torch.as_tensor(P, device=dev), dt)
+    plan.check("helmholtz")
+    e = rel_err(u.cpu().numpy(), ref)
+    plan.close()
+    assert e <= 1e-12, e
