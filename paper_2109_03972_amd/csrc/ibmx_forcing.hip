@@ -523,11 +523,52 @@ __device__ __forceinline__ void reg_get(const T *reg, int RV, int idx, T &x, T &
     z = reg[2 * RV + idx];
 }
 
+// An offset the compiler takes as it is (a select of offsets would become a
+// select of 64-bit addresses), and a line no load above it is moved below
+// (sunk into the branches that use it, it would be waited for at once).
+__device__ __forceinline__ unsigned opaque(unsigned i)
+{
+    asm volatile("" : "+v"(i));
+    return i;
+}
+__device__ __forceinline__ void loads_stay_above() { asm volatile("" ::: "memory"); }
+
+// Node i of an axis of n nodes wrapped into it; false beyond a wall.  No
+// branches: the axes' flags are uniform, but a branch per row and axis would
+// split a staging step's loads into blocks that wait for one another.
+__device__ __forceinline__ bool wrap_node(int n, int periodic, int &i)
+{
+    const int w = i + (i < 0 ? n : 0) - (i >= n ? n : 0);
+    const bool in = (periodic != 0) | (w == i);
+    i = w;
+    return in;
+}
+
+// Row r = rz R1 + ry of a tile's support region: the grid index of its first
+// x = 0 node (false beyond a wall).  The quotient is exact for r < 2^16.
+struct RegionRows {
+    int y0, z0, R1;
+    float inv;
+    __device__ RegionRows(const TileBox &box, int r1)
+        : y0(box.o[1] - 1), z0(box.o[2] - 1), R1(r1), inv(1.0f / (float)r1)
+    {
+    }
+    __device__ bool at(const GridC &g, int r, unsigned &row) const
+    {
+        const int rz = (int)(((float)r + 0.5f) * inv);
+        int gy = y0 + r - rz * R1, gz = z0 + rz;
+        const bool iny = wrap_node(g.n[1], g.periodic[1], gy);
+        const bool inz = wrap_node(g.n[2], g.periodic[2], gz);
+        row = ((unsigned)gz * (unsigned)g.n[1] + (unsigned)gy) * (unsigned)g.n[0];
+        return iny & inz;
+    }
+};
+
 // Stage v = scale * src (+ src2) over the tile's support region
 // [o - 1, o + B + W - 2) per axis into LDS (nodes beyond a wall read 0),
 // element by element: each wave loads 64 / R0 rows of R0 nodes per step, and
 // every thread issues SUNR steps of loads before its LDS stores.
-template <typename T, int W, bool O32>
+template <typename T, int W, bool O32, bool TWO>
 __device__ __forceinline__ void stage_region_rows(const GridC &g, const TileC &tc,
                                                   const TileBox &box, const T *__restrict__ src,
                                                   T scale, const T *__restrict__ src2, T *reg)
@@ -536,7 +577,8 @@ __device__ __forceinline__ void stage_region_rows(const GridC &g, const TileC &t
     const int RV = R0 * R1 * R2;
     const long long N = g.nodes;
     const T *const s1[3] = {src, src + N, src + 2 * N};
-    const T *const s2[3] = {src2, src2 ? src2 + N : nullptr, src2 ? src2 + 2 * N : nullptr};
+    const T *const s2[3] = {src2, TWO ? src2 + N : nullptr, TWO ? src2 + 2 * N : nullptr};
+    constexpr int UN = TWO ? SUNR / 2 : SUNR;
     const int lane = threadIdx.x & (IBMX_WAVE - 1), wave = threadIdx.x / IBMX_WAVE;
     const int nw = blockDim.x / IBMX_WAVE;
     const int rpi = IBMX_WAVE / R0;
@@ -545,46 +587,37 @@ __device__ __forceinline__ void stage_region_rows(const GridC &g, const TileC &t
     int gx = box.o[0] - 1 + rx;
     const bool lane_ok = sub < rpi;
     // a node beyond an x wall is stored as 0 like those beyond y and z walls
-    bool inx = true;
-    if (g.periodic[0])
-        gx = gx < 0 ? gx + g.n[0] : (gx >= g.n[0] ? gx - g.n[0] : gx);
-    else
-        inx = gx >= 0 && gx < g.n[0];
-    for (int r0 = wave * rpi + sub; r0 < rows; r0 += SUNR * step) {
-        T v[SUNR][3];
-        int li[SUNR];
+    const bool inx = wrap_node(g.n[0], g.periodic[0], gx);
+    const RegionRows region(box, R1);
+    for (int r0 = wave * rpi + sub; r0 < rows; r0 += UN * step) {
+        T v[UN][3], v2[UN][3];
+        int li[UN];
+        bool in[UN];
 #pragma unroll
-        for (int q = 0; q < SUNR; ++q) {
+        for (int q = 0; q < UN; ++q) {
             const int r = r0 + q * step;
-            const int rz = r / R1, ry = r - rz * R1;
-            int gy = box.o[1] - 1 + ry, gz = box.o[2] - 1 + rz;
-            bool ok = lane_ok && r < rows;
-            li[q] = ok ? (rz * R1 + ry) * R0 + rx : -1;
-            ok = ok && inx;
-            if (g.periodic[1])
-                gy = gy < 0 ? gy + g.n[1] : (gy >= g.n[1] ? gy - g.n[1] : gy);
-            else
-                ok = ok && gy >= 0 && gy < g.n[1];
-            if (g.periodic[2])
-                gz = gz < 0 ? gz + g.n[2] : (gz >= g.n[2] ? gz - g.n[2] : gz);
-            else
-                ok = ok && gz >= 0 && gz < g.n[2];
-            v[q][0] = v[q][1] = v[q][2] = T(0);
-            if (ok) {
-                const unsigned gi =
-                    ((unsigned)gz * (unsigned)g.n[1] + (unsigned)gy) * (unsigned)g.n[0] + (unsigned)gx;
+            unsigned row;
+            const bool own = lane_ok & (r < rows);
+            in[q] = region.at(g, r, row) & own & inx;
+            li[q] = own ? r * R0 + rx : -1;
+            const unsigned gi = opaque(in[q] ? row + (unsigned)gx : 0u);
 #pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    v[q][c] = scale * grid_at_as<T, T, O32>(s1[c], gi);
-                    if (src2)
-                        v[q][c] += grid_at_as<T, T, O32>(s2[c], gi);
-                }
+            for (int c = 0; c < 3; ++c) {
+                v[q][c] = grid_at_as<T, T, O32>(s1[c], gi);
+                if (TWO)
+                    v2[q][c] = grid_at_as<T, T, O32>(s2[c], gi);
             }
         }
+        loads_stay_above();
 #pragma unroll
-        for (int q = 0; q < SUNR; ++q) {
+        for (int q = 0; q < UN; ++q) {
             if (li[q] < 0)
                 continue;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                v[q][c] = TWO ? scale * v[q][c] + v2[q][c] : scale * v[q][c];
+                v[q][c] = in[q] ? v[q][c] : T(0);
+            }
             reg_put<T>(reg, RV, li[q], v[q][0], v[q][1], v[q][2]);
         }
     }
@@ -596,23 +629,41 @@ struct alignas(16) Pack16 {
     T e[16 / sizeof(T)];
 };
 
+// Waves per SIMD the staging kernels are compiled for: as many as the LDS
+// regions of the usual tiles leave (16 x 16 x 8 nodes: 39 KB in FP32, four
+// workgroups per CU; 78 KB in FP64, two).
+template <typename T>
+constexpr int tile_waves()
+{
+    return sizeof(T) == 4 ? 4 : 2;
+}
+
 // The same staging with 16-byte loads: every row of the region is covered by
 // the aligned packets of [floor_E(o - 1), ceil_E(o + B + W - 2)) (E values
-// per packet); packets inside the grid are loaded whole, packets crossing an
-// edge value by value (wrapped on a periodic axis, 0 beyond a wall).  Needs
-// n_x and the field pointers to be multiples of E values / 16 bytes.
+// per packet).  Needs n_x and the field pointers to be multiples of E values /
+// 16 bytes.  Every packet takes one unconditional load (of the grid's first
+// packet where there is nothing to load, replaced by 0 behind a wall): a load
+// under a condition, or into registers cleared before it, makes the compiler
+// wait for the loads before it, and a step's loads no longer overlap.  What
+// that gave where latency binds: the four-point interpolation on 150 x 133 x
+// 177 nodes, FP32, 40.6 -> 32.8 us; the adjoint's of 128^3, FP64, 79 -> 32 us
+// (with its records below); on 512^3, where the region's bytes bind (4.4 TB/s
+// from memory and L2), nothing (0.71 ms).
 constexpr int VUNR = 5;   // row groups per vector staging step
-template <typename T, int W, bool O32>
+// With a second source (the adjoint) a step holds two fields' packets: three
+// row groups of both in flight fit the 128 VGPRs that four waves per SIMD leave.
+constexpr int VUNR2 = 3;
+template <typename T, int W, bool O32, bool TWO>
 __device__ __forceinline__ void stage_region_vec(const GridC &g, const TileC &tc,
                                                  const TileBox &box, const T *__restrict__ src,
                                                  T scale, const T *__restrict__ src2, T *reg)
 {
-    constexpr int E = 16 / (int)sizeof(T);
+    constexpr int E = 16 / (int)sizeof(T), UN = TWO ? VUNR2 : VUNR;
     const int R0 = tc.B[0] + W - 1, R1 = tc.B[1] + W - 1, R2 = tc.B[2] + W - 1;
     const int RV = R0 * R1 * R2;
     const long long N = g.nodes;
     const T *const s1[3] = {src, src + N, src + 2 * N};
-    const T *const s2[3] = {src2, src2 ? src2 + N : nullptr, src2 ? src2 + 2 * N : nullptr};
+    const T *const s2[3] = {src2, TWO ? src2 + N : nullptr, TWO ? src2 + 2 * N : nullptr};
     const int xs = box.o[0] - 1, xe = box.o[0] + R0 - 1;   // needed x range
     const int X0 = xs >= 0 ? xs - xs % E : -E;               // xs >= -1
     const int nch = (xe + E - 1 - X0) / E;                 // packets per row (xe > 0)
@@ -622,71 +673,34 @@ __device__ __forceinline__ void stage_region_vec(const GridC &g, const TileC &tc
     const int sub = lane / nch, ch = lane - sub * nch;
     const int step = nw * rpi, rows = R1 * R2;
     const int x = X0 + ch * E;
+    // n_x and x are multiples of E: a packet lies wholly inside the grid or
+    // wholly beyond an edge, where it wraps whole (periodic) or is 0 (wall)
+    int xw = x;
+    const bool inx = wrap_node(g.n[0], g.periodic[0], xw);
     const bool lane_ok = sub < rpi;
-    const bool whole = x >= 0 && x + E <= g.n[0];
-    for (int r0 = wave * rpi + sub; r0 < rows; r0 += VUNR * step) {
-        Pack16<T> v[VUNR][3];
-        int rb[VUNR];
+    const RegionRows region(box, R1);
+    for (int r0 = wave * rpi + sub; r0 < rows; r0 += UN * step) {
+        Pack16<T> v[UN][3], v2[UN][3];
+        int rb[UN];
+        bool in[UN];
 #pragma unroll
-        for (int q = 0; q < VUNR; ++q) {
+        for (int q = 0; q < UN; ++q) {
             const int r = r0 + q * step;
-            const int rz = r / R1, ry = r - rz * R1;
-            int gy = box.o[1] - 1 + ry, gz = box.o[2] - 1 + rz;
-            bool ok = lane_ok && r < rows;
-            if (g.periodic[1])
-                gy = gy < 0 ? gy + g.n[1] : (gy >= g.n[1] ? gy - g.n[1] : gy);
-            else
-                ok = ok && gy >= 0 && gy < g.n[1];
-            if (g.periodic[2])
-                gz = gz < 0 ? gz + g.n[2] : (gz >= g.n[2] ? gz - g.n[2] : gz);
-            else
-                ok = ok && gz >= 0 && gz < g.n[2];
-            rb[q] = lane_ok && r < rows ? (rz * R1 + ry) * R0 : -1;
+            unsigned row;
+            const bool own = lane_ok & (r < rows);
+            in[q] = region.at(g, r, row) & own & inx;
+            rb[q] = own ? r * R0 : -1;
+            const unsigned gi = opaque(in[q] ? row + (unsigned)xw : 0u);
 #pragma unroll
-            for (int c = 0; c < 3; ++c)
-#pragma unroll
-                for (int k = 0; k < E; ++k)
-                    v[q][c].e[k] = T(0);
-            if (!ok)
-                continue;
-            const unsigned row = ((unsigned)gz * (unsigned)g.n[1] + (unsigned)gy) * (unsigned)g.n[0];
-            if (whole) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    v[q][c] = grid_at_as<Pack16<T>, T, O32>(s1[c], row + (unsigned)x);
-                    if (src2) {
-                        const Pack16<T> w2 = grid_at_as<Pack16<T>, T, O32>(s2[c], row + (unsigned)x);
-#pragma unroll
-                        for (int k = 0; k < E; ++k)
-                            v[q][c].e[k] = scale * v[q][c].e[k] + w2.e[k];
-                    } else if (scale != T(1)) {
-#pragma unroll
-                        for (int k = 0; k < E; ++k)
-                            v[q][c].e[k] = scale * v[q][c].e[k];
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int k = 0; k < E; ++k) {
-                    int gx = x + k;
-                    if (gx < xs || gx >= xe)
-                        continue;
-                    if (g.periodic[0])
-                        gx = gx < 0 ? gx + g.n[0] : (gx >= g.n[0] ? gx - g.n[0] : gx);
-                    else if (gx < 0 || gx >= g.n[0])
-                        continue;
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        T val = scale * grid_at_as<T, T, O32>(s1[c], row + (unsigned)gx);
-                        if (src2)
-                            val += grid_at_as<T, T, O32>(s2[c], row + (unsigned)gx);
-                        v[q][c].e[k] = val;
-                    }
-                }
+            for (int c = 0; c < 3; ++c) {
+                v[q][c] = grid_at_as<Pack16<T>, T, O32>(s1[c], gi);
+                if (TWO)
+                    v2[q][c] = grid_at_as<Pack16<T>, T, O32>(s2[c], gi);
             }
         }
+        loads_stay_above();
 #pragma unroll
-        for (int q = 0; q < VUNR; ++q) {
+        for (int q = 0; q < UN; ++q) {
             if (rb[q] < 0)
                 continue;
 #pragma unroll
@@ -694,13 +708,19 @@ __device__ __forceinline__ void stage_region_vec(const GridC &g, const TileC &tc
                 const int lx = x + k - xs;
                 if (lx < 0 || lx >= R0)
                     continue;
-                reg_put<T>(reg, RV, rb[q] + lx, v[q][0].e[k], v[q][1].e[k], v[q][2].e[k]);
+                T w[3];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    w[c] = TWO ? scale * v[q][c].e[k] + v2[q][c].e[k] : scale * v[q][c].e[k];
+                    w[c] = in[q] ? w[c] : T(0);
+                }
+                reg_put<T>(reg, RV, rb[q] + lx, w[0], w[1], w[2]);
             }
         }
     }
 }
 
-template <typename T, int W, bool O32 = false>
+template <typename T, int W, bool O32, bool MAY_TWO = false>
 __device__ __forceinline__ void stage_region(const GridC &g, const TileC &tc, const TileBox &box,
                                              const T *__restrict__ src, T scale,
                                              const T *__restrict__ src2, T *reg)
@@ -708,10 +728,16 @@ __device__ __forceinline__ void stage_region(const GridC &g, const TileC &tc, co
     constexpr int E = 16 / (int)sizeof(T);
     const bool vec = g.n[0] % E == 0 && ((size_t)src & 15) == 0 &&
                      (!src2 || ((size_t)src2 & 15) == 0);
-    if (vec)
-        stage_region_vec<T, W, O32>(g, tc, box, src, scale, src2, reg);
-    else
-        stage_region_rows<T, W, O32>(g, tc, box, src, scale, src2, reg);
+    if (MAY_TWO && src2) {
+        if (vec)
+            stage_region_vec<T, W, O32, true>(g, tc, box, src, scale, src2, reg);
+        else
+            stage_region_rows<T, W, O32, true>(g, tc, box, src, scale, src2, reg);
+    } else if (vec) {
+        stage_region_vec<T, W, O32, false>(g, tc, box, src, scale, src2, reg);
+    } else {
+        stage_region_rows<T, W, O32, false>(g, tc, box, src, scale, src2, reg);
+    }
 }
 
 // Region index of a marker's base node per axis: the centre node b + 1 lies
@@ -1166,12 +1192,10 @@ __device__ __forceinline__ void interp_tile(int tile, const GridC &g, const Tile
     const TileBox box(g, tc, tile);
     const int R0 = tc.B[0] + W - 1, R1 = tc.B[1] + W - 1, R2 = tc.B[2] + W - 1;
     const int RV = R0 * R1 * R2;
-    // first records of this thread, in flight during the staging
-    T4 tn = {}, ud = {};
-    if ((int)threadIdx.x < n_own) {
-        tn = rec_tn[a0 + threadIdx.x];
-        ud = rec_ud[a0 + threadIdx.x];
-    }
+    // first records of this thread (some record of the tile where it has
+    // none), in flight during the staging
+    const int jf = a0 + min((int)threadIdx.x, n_own - 1);
+    T4 tn = rec_tn[jf], ud = rec_ud[jf];
     stage_region<T, W, O32>(g, tc, box, u, T(1), (const T *)nullptr, reg);
     __syncthreads();
     float gmax[3] = {0.f, 0.f, 0.f};
@@ -1247,7 +1271,7 @@ __device__ __forceinline__ void interp_tile(int tile, const GridC &g, const Tile
 }
 
 template <typename T, int W, int MODE, bool O32, bool PERSIST>
-__global__ __launch_bounds__(256) void k_interp(
+__global__ __launch_bounds__(256, tile_waves<T>()) void k_interp(
     GridC g, TileC tc, int nm, int pass, double c, const int *__restrict__ tile_start,
     const typename V4<T>::type *__restrict__ rec_tn, const typename V4<T>::type *__restrict__ rec_ud,
     const int *__restrict__ rec_src, const T *__restrict__ u,
@@ -1361,9 +1385,10 @@ __global__ __launch_bounds__(256) void k_particle_sums(
 // and finally g_u0 = ub, g_up = sum Udb, g_wp = sum o x Udb, g_xp = sum Xb.
 // ---------------------------------------------------------------------------
 
-// Forward replay of one pass: U, G and J for own markers (LDS-staged u).
-template <typename T, int W>
-__global__ __launch_bounds__(256) void k_interp_jac(
+// Forward replay of one pass: U, G and J for own markers (LDS-staged u), the
+// first records of every thread in flight during the staging.
+template <typename T, int W, bool O32>
+__global__ __launch_bounds__(256, tile_waves<T>()) void k_interp_jac(
     GridC g, TileC tc, int nm, double c, const int *__restrict__ tile_start,
     const typename V4<T>::type *__restrict__ rec_tn, const typename V4<T>::type *__restrict__ rec_ud,
     const T *__restrict__ u, typename V4<T>::type *__restrict__ GJ)
@@ -1377,12 +1402,18 @@ __global__ __launch_bounds__(256) void k_interp_jac(
         return;
     const TileBox box(g, tc, tile);
     const int R0 = tc.B[0] + W - 1, R1 = tc.B[1] + W - 1, RV = R0 * R1 * (tc.B[2] + W - 1);
-    stage_region<T, W>(g, tc, box, u, T(1), (const T *)nullptr, reg);
+    const int jf = a0 + min((int)threadIdx.x, n_own - 1);
+    T4 ptn = rec_tn[jf], pud = rec_ud[jf];
+    stage_region<T, W, O32>(g, tc, box, u, T(1), (const T *)nullptr, reg);
     __syncthreads();
     const T inv_h = (T)(1.0 / g.h);
     for (int e = threadIdx.x; e < n_own; e += blockDim.x) {
         const int j = a0 + e;
-        const T4 tn = rec_tn[j], ud = rec_ud[j];
+        const T4 tn = ptn, ud = pud;
+        if (e + (int)blockDim.x < n_own) {
+            ptn = rec_tn[j + blockDim.x];
+            pud = rec_ud[j + blockDim.x];
+        }
         const T tt[3] = {tn.x, tn.y, tn.z};
         int b[3], d[3];
         unpack_node(g, V4<T>::to_bits(tn.w), b);
@@ -1437,17 +1468,50 @@ __global__ __launch_bounds__(256) void k_interp_jac(
     }
 }
 
+// The pass-independent part of Fb of every record, {dV (g_S + g_T x o), dV}
+// in record order (FP64): the passes then read one coalesced record instead
+// of following record -> marker -> particle through three scattered loads
+// (k_interp_adj on the 256 x 256 x 512 bed, FP32: 426 -> 409 us with this and
+// the two sums packed, -> 327 us with both fields' staging loads in flight;
+// what it moves, 0.86 GB, at 2.6 TB/s).
+__global__ __launch_bounds__(256) void k_adj_static(int ntiles, int nm, int np,
+                                                    const int *__restrict__ tile_start,
+                                                    const int *__restrict__ rec_src,
+                                                    const double *__restrict__ body,
+                                                    const int *__restrict__ pid_of,
+                                                    const double *__restrict__ dV,
+                                                    const double *__restrict__ gS,
+                                                    const double *__restrict__ gT,
+                                                    double4 *__restrict__ fst)
+{
+    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= tile_start[ntiles])
+        return;
+    const int l = rec_src[j], pid = pid_of[l];
+    const double o[3] = {body[l], body[(size_t)nm + l], body[2 * (size_t)nm + l]};
+    const double dVp = dV[pid];
+    double gs[3] = {0.0, 0.0, 0.0}, gt[3] = {0.0, 0.0, 0.0};
+    for (int a = 0; a < 3; ++a) {
+        if (gS)
+            gs[a] = gS[(size_t)a * np + pid];
+        if (gT)
+            gt[a] = gT[(size_t)a * np + pid];
+    }
+    const double gtxo[3] = {gt[1] * o[2] - gt[2] * o[1], gt[2] * o[0] - gt[0] * o[2],
+                            gt[0] * o[1] - gt[1] * o[0]};
+    fst[j] = make_double4(dVp * (gs[0] + gtxo[0]), dVp * (gs[1] + gtxo[1]),
+                          dVp * (gs[2] + gtxo[2]), dVp);
+}
+
 // Adjoint interpolation of one pass (own markers): Ub for the spreading,
-// and the per-marker accumulation of Udb and Xb.
-template <typename T, int W, int FIRST>
-__global__ __launch_bounds__(256) void k_interp_adj(
-    GridC g, TileC tc, int nm, int np, double c, const int *__restrict__ tile_start,
-    const typename V4<T>::type *__restrict__ rec_tn, const int *__restrict__ rec_src,
-    const double *__restrict__ body, const int *__restrict__ pid_of,
-    const double *__restrict__ dV, const double *__restrict__ gS, const double *__restrict__ gT,
+// and the per-marker accumulation of Udb and Xb (acc: double2[3][nm], {Udb_x,
+// Udb_y}, {Udb_z, Xb_x}, {Xb_y, Xb_z}).
+template <typename T, int W, int FIRST, bool O32>
+__global__ __launch_bounds__(256, tile_waves<T>()) void k_interp_adj(
+    GridC g, TileC tc, int nm, double c, const int *__restrict__ tile_start,
+    const typename V4<T>::type *__restrict__ rec_tn, const double4 *__restrict__ fst,
     const T *__restrict__ ub, const T *__restrict__ gf, const typename V4<T>::type *__restrict__ GJ,
-    typename V4<T>::type *__restrict__ Ub_out, double4 *__restrict__ accA,
-    double4 *__restrict__ accB)
+    typename V4<T>::type *__restrict__ Ub_out, double2 *__restrict__ acc)
 {
     typedef typename V4<T>::type T4;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1458,17 +1522,27 @@ __global__ __launch_bounds__(256) void k_interp_adj(
         return;
     const TileBox box(g, tc, tile);
     const int R0 = tc.B[0] + W - 1, R1 = tc.B[1] + W - 1, RV = R0 * R1 * (tc.B[2] + W - 1);
-    stage_region<T, W>(g, tc, box, ub, (T)c, gf, reg);   // fb = c ub + g_f
+    // the first records of this thread, in flight during the staging
+    T4 ptn, pq0, pq1, pq2;
+    double4 pfs;
+    auto load = [&](int j) {
+        ptn = rec_tn[j];
+        pq0 = GJ[j];
+        pq1 = GJ[nm + j];
+        pq2 = GJ[2 * (size_t)nm + j];
+        pfs = fst[j];
+    };
+    load(a0 + min((int)threadIdx.x, n_own - 1));
+    stage_region<T, W, O32, true>(g, tc, box, ub, (T)c, gf, reg);   // fb = c ub + g_f
     __syncthreads();
     const double inv_h = 1.0 / g.h;
     for (int e = threadIdx.x; e < n_own; e += blockDim.x) {
         const int j = a0 + e;
-        const T4 tn = rec_tn[j];
-        const int l = rec_src[j];
+        const T4 tn = ptn, q0 = pq0, q1 = pq1, q2 = pq2;
+        const double4 fs = pfs;
+        if (e + (int)blockDim.x < n_own)
+            load(j + blockDim.x);
         const T tt[3] = {tn.x, tn.y, tn.z};
-        const double o[3] = {body[l], body[(size_t)nm + l], body[2 * (size_t)nm + l]};
-        const int pid = pid_of[l];
-        const T4 q0 = GJ[j], q1 = GJ[nm + j], q2 = GJ[2 * (size_t)nm + j];
         const T G[3] = {q0.x, q0.y, q0.z};
         const double Jm[3][3] = {{(double)q0.w, (double)q1.x, (double)q1.y},
                                  {(double)q1.z, (double)q1.w, (double)q2.x},
@@ -1499,21 +1573,13 @@ __global__ __launch_bounds__(256) void k_interp_adj(
                     P[2] += dw[2][k] * w[1][jj] * w[0][i] * fg;
                 }
             }
-        const double dVp = dV[pid], v = dVp * g.inv_h3;
-        double gs[3] = {0.0, 0.0, 0.0}, gt[3] = {0.0, 0.0, 0.0};
-        for (int a = 0; a < 3; ++a) {
-            if (gS)
-                gs[a] = gS[(size_t)a * np + pid];
-            if (gT)
-                gt[a] = gT[(size_t)a * np + pid];
-        }
-        const double gtxo[3] = {gt[1] * o[2] - gt[2] * o[1], gt[2] * o[0] - gt[0] * o[2],
-                                gt[0] * o[1] - gt[1] * o[0]};
+        const double v = fs.w * g.inv_h3;
+        const double fsv[3] = {fs.x, fs.y, fs.z};
         double Ubv[3], Udb[3];
         for (int a = 0; a < 3; ++a) {
-            const double Fb = v * (double)IF[a] + dVp * (gs[a] + gtxo[a]);
-            Ubv[a] = -Fb / c;
+            const double Fb = v * (double)IF[a] + fsv[a];
             Udb[a] = Fb / c;
+            Ubv[a] = -Udb[a];
         }
         double Xb[3];
         for (int a = 0; a < 3; ++a)
@@ -1524,19 +1590,17 @@ __global__ __launch_bounds__(256) void k_interp_adj(
         ubo.z = (T)Ubv[2];
         ubo.w = T(0);
         Ub_out[j] = ubo;
-        double4 A = make_double4(Udb[0], Udb[1], Udb[2], 0.0);
-        double4 B = make_double4(Xb[0], Xb[1], Xb[2], 0.0);
-        if (!FIRST) {
-            const double4 A0 = accA[j], B0 = accB[j];
-            A.x += A0.x;
-            A.y += A0.y;
-            A.z += A0.z;
-            B.x += B0.x;
-            B.y += B0.y;
-            B.z += B0.z;
+        double2 A[3] = {make_double2(Udb[0], Udb[1]), make_double2(Udb[2], Xb[0]),
+                        make_double2(Xb[1], Xb[2])};
+        for (int q = 0; q < 3; ++q) {
+            double2 *p = acc + (size_t)q * nm + j;
+            if (!FIRST) {
+                const double2 o = *p;
+                A[q].x += o.x;
+                A[q].y += o.y;
+            }
+            *p = A[q];
         }
-        accA[j] = A;
-        accB[j] = B;
     }
 }
 
@@ -1544,8 +1608,7 @@ __global__ __launch_bounds__(256) void k_interp_adj(
 __global__ __launch_bounds__(256) void k_particle_grad(int np, int nm, const int *__restrict__ moff,
                                                        const double *__restrict__ body,
                                                        const int *__restrict__ m_inv,
-                                                       const double4 *__restrict__ accA,
-                                                       const double4 *__restrict__ accB,
+                                                       const double2 *__restrict__ acc,
                                                        double *__restrict__ gxp,
                                                        double *__restrict__ gup,
                                                        double *__restrict__ gwp)
@@ -1559,17 +1622,17 @@ __global__ __launch_bounds__(256) void k_particle_grad(int np, int nm, const int
         const int j = m_inv[l];
         if (j < 0)
             continue;
-        const double4 A = accA[j], B = accB[j];
+        const double2 a0 = acc[j], a1 = acc[(size_t)nm + j], a2 = acc[2 * (size_t)nm + j];
         const double o[3] = {body[l], body[(size_t)nm + l], body[2 * (size_t)nm + l]};
-        sm[0] += A.x;
-        sm[1] += A.y;
-        sm[2] += A.z;
-        sm[3] += o[1] * A.z - o[2] * A.y;
-        sm[4] += o[2] * A.x - o[0] * A.z;
-        sm[5] += o[0] * A.y - o[1] * A.x;
-        sm[6] += B.x;
-        sm[7] += B.y;
-        sm[8] += B.z;
+        sm[0] += a0.x;
+        sm[1] += a0.y;
+        sm[2] += a1.x;
+        sm[3] += o[1] * a1.x - o[2] * a0.y;
+        sm[4] += o[2] * a0.x - o[0] * a1.x;
+        sm[5] += o[0] * a0.y - o[1] * a0.x;
+        sm[6] += a1.y;
+        sm[7] += a2.x;
+        sm[8] += a2.y;
     }
 #pragma unroll
     for (int q = 0; q < 9; ++q)
@@ -1812,7 +1875,7 @@ ibmx_status run_forcing(ibmx_plan p, T *u, T *f_tot, const double *xp, const dou
     return ibmx_launch_check();
 }
 
-template <typename T, int W>
+template <typename T, int W, bool O32>
 ibmx_status run_backward(ibmx_plan p, const T *u0, const double *xp, const double *up,
                          const double *wp, const uint8_t *mask, const T *g_f, const T *g_u,
                          const double *g_S, const double *g_T, T *gu0, double *gxp, double *gup,
@@ -1831,9 +1894,9 @@ ibmx_status run_backward(ibmx_plan p, const T *u0, const double *xp, const doubl
     if (!p->bw_u || p->bw_bytes < ibmx_backward_bytes(p))
         return IBMX_ESTATE;
     T *us = (T *)p->bw_u;
-    T4 *GJ = (T4 *)(us + G3);
-    double4 *accA = (double4 *)(GJ + 3 * (size_t)nm * p->n_iter_cap);
-    double4 *accB = accA + nm;
+    T4 *GJ = (T4 *)(us + (G3 + 15) / 16 * 16);   // records start on 64 bytes
+    double4 *fst = (double4 *)(GJ + 3 * (size_t)nm * p->n_iter_cap);
+    double2 *acc = (double2 *)(fst + nm);
     bin_markers<T, W>(p, xp, up, wp, mask);
     const int cb = 4096;
     {
@@ -1850,41 +1913,48 @@ ibmx_status run_backward(ibmx_plan p, const T *u0, const double *xp, const doubl
     if (nm > 0) {
         const size_t lds_i = interp_lds<T, W>(tc), lds_s = spread_lds<T>(tc);
         ProfScope ps(p, IBMX_K_BACKWARD);
+        hipLaunchKernelGGL(k_adj_static, dim3(nblocks(nm, 256)), dim3(256), 0, s, ntiles, nm, np,
+                           (const int *)p->tile_start, (const int *)p->rec_src, p->body,
+                           (const int *)p->d_pid, p->dV, g_S, g_T, fst);
         for (int m = 0; m < n_iter; ++m) {
             T4 *GJm = GJ + 3 * (size_t)nm * m;
-            hipLaunchKernelGGL((k_interp_jac<T, W>), dim3(ntiles), dim3(256), lds_i, s, p->g, tc, nm,
-                               c, p->tile_start, (const T4 *)rec_tn, (const T4 *)rec_ud,
+            hipLaunchKernelGGL((k_interp_jac<T, W, O32>), dim3(ntiles), dim3(256), lds_i, s, p->g,
+                               tc, nm, c, p->tile_start, (const T4 *)rec_tn, (const T4 *)rec_ud,
                                (const T *)us, GJm);
             if (m < n_iter - 1)
-                launch_spread<T, W>(p, lds_s, s, p->g, tc, (T)c, 1, 0, 0,
-                                    (const int *)p->tile_start, (const int *)p->halo_start,
-                                    (const int *)p->halo_list, (const T4 *)rec_tn,
-                                    (const T4 *)GJm, (const float4 *)nullptr, us, (T *)nullptr,
-                                    p->d_count);
+                launch_spread_k<T, W, O32, true, false>(
+                    p, lds_s, s, p->g, tc, (T)c, 0, (const int *)p->tile_start,
+                    (const int *)p->halo_start, (const int *)p->halo_list, (const T4 *)rec_tn,
+                    (const T4 *)GJm, (const float4 *)nullptr, us, (T *)nullptr, p->d_count);
         }
         for (int m = n_iter - 1; m >= 0; --m) {
             const T4 *GJm = GJ + 3 * (size_t)nm * m;
             if (m == n_iter - 1)
-                hipLaunchKernelGGL((k_interp_adj<T, W, 1>), dim3(ntiles), dim3(256), lds_i, s, p->g,
-                                   tc, nm, np, c, p->tile_start, (const T4 *)rec_tn,
-                                   p->rec_src, p->body, p->d_pid, p->dV, g_S, g_T,
-                                   (const T *)gu0, g_f, GJm, rec_Ub, accA, accB);
+                hipLaunchKernelGGL((k_interp_adj<T, W, 1, O32>), dim3(ntiles), dim3(256), lds_i, s,
+                                   p->g, tc, nm, c, p->tile_start, (const T4 *)rec_tn,
+                                   (const double4 *)fst, (const T *)gu0, g_f, GJm, rec_Ub, acc);
             else
-                hipLaunchKernelGGL((k_interp_adj<T, W, 0>), dim3(ntiles), dim3(256), lds_i, s, p->g,
-                                   tc, nm, np, c, p->tile_start, (const T4 *)rec_tn,
-                                   p->rec_src, p->body, p->d_pid, p->dV, g_S, g_T,
-                                   (const T *)gu0, g_f, GJm, rec_Ub, accA, accB);
-            launch_spread<T, W>(p, lds_s, s, p->g, tc, T(1), 1, 0, 0, (const int *)p->tile_start,
-                                (const int *)p->halo_start, (const int *)p->halo_list,
-                                (const T4 *)rec_tn, (const T4 *)rec_Ub, (const float4 *)nullptr,
-                                gu0, (T *)nullptr, p->d_count);
+                hipLaunchKernelGGL((k_interp_adj<T, W, 0, O32>), dim3(ntiles), dim3(256), lds_i, s,
+                                   p->g, tc, nm, c, p->tile_start, (const T4 *)rec_tn,
+                                   (const double4 *)fst, (const T *)gu0, g_f, GJm, rec_Ub, acc);
+            launch_spread_k<T, W, O32, true, false>(
+                p, lds_s, s, p->g, tc, T(1), 0, (const int *)p->tile_start,
+                (const int *)p->halo_start, (const int *)p->halo_list, (const T4 *)rec_tn,
+                (const T4 *)rec_Ub, (const float4 *)nullptr, gu0, (T *)nullptr, p->d_count);
         }
         if (np > 0)
             hipLaunchKernelGGL(k_particle_grad, dim3(nblocks(np, 4)), dim3(256), 0, s, np, nm,
-                               p->d_moff, p->body, p->m_inv, (const double4 *)accA,
-                               (const double4 *)accB, gxp, gup, gwp);
+                               p->d_moff, p->body, p->m_inv, (const double2 *)acc, gxp, gup,
+                               gwp);
     }
     return ibmx_launch_check();
+}
+
+template <typename T, int W, typename... A>
+ibmx_status launch_backward(ibmx_plan p, A... args)
+{
+    return offsets32<T>(p) ? run_backward<T, W, true>(p, args...)
+                           : run_backward<T, W, false>(p, args...);
 }
 
 template <typename T, int W>
@@ -1916,8 +1986,12 @@ hipError_t allow_lds_w(int bytes_interp, int bytes_spread)
                              (const void *)k_interp<T, W, 2, true, true>,
                              (const void *)k_interp<T, W, 0, false, true>,
                              (const void *)k_interp<T, W, 2, false, true>,
-                             (const void *)k_interp_jac<T, W>,
-                             (const void *)k_interp_adj<T, W, 0>, (const void *)k_interp_adj<T, W, 1>};
+                             (const void *)k_interp_jac<T, W, true>,
+                             (const void *)k_interp_jac<T, W, false>,
+                             (const void *)k_interp_adj<T, W, 0, true>,
+                             (const void *)k_interp_adj<T, W, 0, false>,
+                             (const void *)k_interp_adj<T, W, 1, true>,
+                             (const void *)k_interp_adj<T, W, 1, false>};
     for (const void *f : interps)
         if ((e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes_interp)) !=
             hipSuccess)
@@ -1928,13 +2002,14 @@ hipError_t allow_lds_w(int bytes_interp, int bytes_spread)
 }  // namespace
 
 // Adjoint workspace: the replay grid T[3][nodes], per-pass amplitude and
-// Jacobian T4[n_iter][3][nm], two double4[nm] per-marker sums.
+// Jacobian T4[n_iter][3][nm], the pass-independent double4[nm] and the
+// double2[3][nm] sums of every marker.
 size_t ibmx_backward_bytes(ibmx_plan p)
 {
     const size_t Ts = p->prec == IBMX_F64 ? sizeof(double) : sizeof(float);
     const size_t nm = (size_t)(p->nm > 0 ? p->nm : 1);
-    return Ts * 3 * (size_t)p->g.nodes + 3 * 4 * Ts * nm * (size_t)p->n_iter_cap +
-           2 * sizeof(double4) * nm;
+    return Ts * ((3 * (size_t)p->g.nodes + 15) / 16 * 16) + 3 * 4 * Ts * nm * (size_t)p->n_iter_cap +
+           (sizeof(double4) + 3 * sizeof(double2)) * nm;
 }
 
 // Allow the tile kernels the plan's LDS footprint (above 64 KB needs an
@@ -2004,18 +2079,18 @@ extern "C" ibmx_status ibmx_forcing_backward(ibmx_plan p, const void *u0, const 
     const int W = p->prm.kernel;
     if (p->prec == IBMX_F64) {
         if (W == 3)
-            return run_backward<double, 3>(p, (const double *)u0, xp, up, wp, marker_active,
+            return launch_backward<double, 3>(p, (const double *)u0, xp, up, wp, marker_active,
                                            (const double *)g_f, (const double *)g_u, g_S, g_T,
                                            (double *)gu0, gxp, gup, gwp);
-        return run_backward<double, 4>(p, (const double *)u0, xp, up, wp, marker_active,
+        return launch_backward<double, 4>(p, (const double *)u0, xp, up, wp, marker_active,
                                        (const double *)g_f, (const double *)g_u, g_S, g_T,
                                        (double *)gu0, gxp, gup, gwp);
     }
     if (W == 3)
-        return run_backward<float, 3>(p, (const float *)u0, xp, up, wp, marker_active,
+        return launch_backward<float, 3>(p, (const float *)u0, xp, up, wp, marker_active,
                                       (const float *)g_f, (const float *)g_u, g_S, g_T,
                                       (float *)gu0, gxp, gup, gwp);
-    return run_backward<float, 4>(p, (const float *)u0, xp, up, wp, marker_active,
+    return launch_backward<float, 4>(p, (const float *)u0, xp, up, wp, marker_active,
                                   (const float *)g_f, (const float *)g_u, g_S, g_T, (float *)gu0,
                                   gxp, gup, gwp);
 }
