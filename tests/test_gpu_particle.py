@@ -82,3 +82,31 @@ def test_grid_mean_of_the_ibm_force(precision):
     cons = S.sum(dim=1).cpu().numpy() / (nodes * case.h ** 3)
     tol = 1e-10 if precision == "f64" else 1e-5
     assert np.abs(got - cons).max() <= tol * np.abs(S.cpu().numpy()).sum() / nodes
+
+
+@pytest.mark.parametrize("count", [1, 511, 512, 4095, 4096])
+def test_integrals_waves_per_particle(count):
+    """The split of a particle over waves changes with the particle count, its
+    rows over lanes with its size (box edges of 3 to 73 cells, over one wave
+    of 64 and the seams): the same spheres in every split against the oracle,
+    FP64 sums in another order (1e-12)."""
+    import torch
+    from paper_2109_03972_amd import ibmx
+    dev = require_gpu()
+    rng = np.random.default_rng(count)
+    n = (150, 80, 160)
+    big = np.array([[3.2, 19.0, 70.0], [140.1, 79.7, 2.5]]).T
+    x = np.concatenate([big, rng.random((3, max(count - 2, 0))) * np.array(n)[:, None]], 1)[:, :count]
+    R = np.concatenate([[36.4, 18.2], rng.uniform(0.6, 2.5, max(count - 2, 0))])[:count]
+    case = synth.small_case(5, n=n, periodic=(1, 1, 0), diameters=(6.0,), disable_mode=0)
+    case.xp, case.up, case.wp = np.ascontiguousarray(x), np.zeros((3, count)), np.zeros((3, count))
+    case.radius, case.mass = R, np.ones(count)
+    case.moff, case.body, case.dV = np.zeros(count + 1, np.int32), np.zeros((3, 0)), np.ones(count)
+    ref = oracle.particle_integrals(case, u=case.u0)
+    plan = ibmx.Plan.from_case(case, "f64")
+    t = lambda a: torch.as_tensor(a, device=dev).contiguous()
+    Iu, Ir = plan.particle_integrals(t(case.u0), t(case.xp), t(case.radius))
+    plan.check("integrals")
+    for k, got in (("Iu", Iu), ("Ir", Ir)):
+        assert rel_err(got.cpu().numpy(), ref[k]) <= 1e-12, k
+    plan.close()
