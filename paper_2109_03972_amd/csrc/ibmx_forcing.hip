@@ -1291,8 +1291,8 @@ __global__ __launch_bounds__(256, tile_waves<T>()) void k_interp(
     }
 }
 
-// Particle sums after the passes, one wave per particle, markers in index
-// order (64 at a time) and passes in order, all in FP64:
+// Particle sums after more than kFewPasses passes, one wave per particle,
+// markers in index order (64 at a time) and passes in order, all in FP64:
 //   S_p = h^3 sum_l sum_m G_l^m,  T_p = h^3 sum_l o_l x sum_m G_l^m,
 //   rpart[m][p] = sum_l dV |U^d - U^m|^2 (m <= n_iter, the last from the
 //   residual pass on the final velocity, when want_res),
@@ -1368,6 +1368,106 @@ __global__ __launch_bounds__(256) void k_particle_sums(
     if (want_res && lane == 0)
         for (int m = 0; m <= n_iter; ++m)
             rpart[(size_t)m * np + p] = racc[wv][m];
+}
+
+// The same sums for calls of NP passes (up to kFewPasses), which hold a
+// marker's amplitudes of every pass in registers: all their loads are in
+// flight together, the next markers' slots are loaded meanwhile, and the
+// residual terms are summed per lane, across lanes once at the end.  BLOCK: the
+// waves of one workgroup share a particle (markers dealt 64 at a time),
+// otherwise one wave takes it and a workgroup four particles; which of the two
+// depends on the plan's particle and marker counts alone.  Latency bound where
+// particles are few: 150 spheres, FP32, three passes 8.4 us against 64 with a
+// wave per particle that loaded pass by pass; the 2000 spheres of the 256 x 256
+// x 512 bed, five passes, 48 against 103; 512^3 bed (bytes: whole lines for
+// scattered 16-byte records) 367 against 410.
+constexpr int kFewPasses = 8;
+template <typename T, int NP, bool BLOCK>
+__global__ __launch_bounds__(BLOCK ? 1024 : 256) void k_particle_sums_few(
+    int np, int nm, int want_res, double h3, const int *__restrict__ moff,
+    const double *__restrict__ body, const int *__restrict__ m_inv,
+    const typename V4<T>::type *__restrict__ rec_Gm, typename V4<T>::type *__restrict__ rec_Gs,
+    double *__restrict__ S_out, double *__restrict__ T_out, double *__restrict__ rpart)
+{
+    typedef typename V4<T>::type T4;
+    constexpr int NS = 6 + NP + 1;
+    __shared__ double part[BLOCK ? 16 : 1][NS];
+    const int wv = threadIdx.x / IBMX_WAVE, lane = threadIdx.x & (IBMX_WAVE - 1);
+    const int nw = BLOCK ? blockDim.x / IBMX_WAVE : 1;
+    const int p = BLOCK ? blockIdx.x : blockIdx.x * 4 + wv;
+    if (!BLOCK && p >= np)
+        return;
+    double sm[NS] = {};
+    const int l0 = moff[p], l1 = moff[p + 1], step = nw * IBMX_WAVE;
+    int l = l0 + (BLOCK ? wv : 0) * IBMX_WAVE + lane;
+    int j = l < l1 ? m_inv[l] : -1;
+    for (; l - lane < l1; l += step) {
+        const int jc = j >= 0 ? j : 0, lc = min(l, l1 - 1);
+        T4 gv[NP];
+#pragma unroll
+        for (int m = 0; m < NP; ++m)
+            gv[m] = rec_Gm[(size_t)m * nm + jc];
+        const double o[3] = {body[lc], body[(size_t)nm + lc], body[2 * (size_t)nm + lc]};
+        const T rl = want_res ? reinterpret_cast<const T *>(rec_Gs + jc)[3] : T(0);
+        const int jn = l + step < l1 ? m_inv[l + step] : -1;
+        if (j >= 0) {
+            double G[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+            for (int m = 0; m < NP; ++m) {
+                G[0] += (double)gv[m].x;
+                G[1] += (double)gv[m].y;
+                G[2] += (double)gv[m].z;
+                sm[6 + m] += (double)gv[m].w;
+            }
+            sm[6 + NP] += (double)rl;
+            T4 gs;
+            gs.x = (T)G[0];
+            gs.y = (T)G[1];
+            gs.z = (T)G[2];
+            gs.w = T(0);
+            rec_Gs[j] = gs;
+            sm[0] += G[0];
+            sm[1] += G[1];
+            sm[2] += G[2];
+            sm[3] += o[1] * G[2] - o[2] * G[1];
+            sm[4] += o[2] * G[0] - o[0] * G[2];
+            sm[5] += o[0] * G[1] - o[1] * G[0];
+        }
+        j = jn;
+    }
+    const int ns = want_res ? NS : 6;
+#pragma unroll
+    for (int q = 0; q < NS; ++q)
+        if (q < ns)
+            sm[q] = wave_sum(sm[q]);
+    if (BLOCK) {
+        if (lane == 0)
+            for (int q = 0; q < ns; ++q)
+                part[wv][q] = sm[q];
+        __syncthreads();
+        if ((int)threadIdx.x >= ns)
+            return;
+        double v = part[0][threadIdx.x];
+        for (int w = 1; w < nw; ++w)
+            v += part[w][threadIdx.x];
+        const int q = threadIdx.x;
+        if (q < 3)
+            S_out[(size_t)q * np + p] = h3 * v;
+        else if (q < 6)
+            T_out[(size_t)(q - 3) * np + p] = h3 * v;
+        else
+            rpart[(size_t)(q - 6) * np + p] = v;
+        return;
+    }
+    if (lane != 0)
+        return;
+    for (int a = 0; a < 3; ++a) {
+        S_out[(size_t)a * np + p] = h3 * sm[a];
+        T_out[(size_t)a * np + p] = h3 * sm[3 + a];
+    }
+    if (want_res)
+        for (int m = 0; m <= NP; ++m)
+            rpart[(size_t)m * np + p] = sm[6 + m];
 }
 
 // ---------------------------------------------------------------------------
@@ -1803,6 +1903,46 @@ void bin_markers(ibmx_plan p, const double *xp, const double *up, const double *
     }
 }
 
+template <typename T, int NP>
+void launch_sums_few(ibmx_plan p, int want_res, double h3, const typename V4<T>::type *Gm,
+                     typename V4<T>::type *Gs, double *S_out, double *T_out)
+{
+    // one wave per particle where the particles fill the chip, else as many
+    // as the average particle's markers take (at most 4, or 16 for fewer than
+    // 512 particles)
+    const int np = p->np, nm = p->nm;
+    const int chunks = (nm / np + IBMX_WAVE - 1) / IBMX_WAVE, most = np < 512 ? 16 : 4;
+    const int waves = np >= 4096 ? 1 : (chunks < most ? (chunks > 1 ? chunks : 1) : most);
+    if (waves == 1)
+        hipLaunchKernelGGL((k_particle_sums_few<T, NP, false>), dim3(nblocks(np, 4)), dim3(256), 0,
+                           p->stream, np, nm, want_res, h3, (const int *)p->d_moff, p->body,
+                           (const int *)p->m_inv, Gm, Gs, S_out, T_out, p->rpart);
+    else
+        hipLaunchKernelGGL((k_particle_sums_few<T, NP, true>), dim3(np), dim3(IBMX_WAVE * waves),
+                           0, p->stream, np, nm, want_res, h3, (const int *)p->d_moff, p->body,
+                           (const int *)p->m_inv, Gm, Gs, S_out, T_out, p->rpart);
+}
+
+template <typename T>
+void launch_sums(ibmx_plan p, int n_iter, int want_res, const typename V4<T>::type *Gm,
+                 typename V4<T>::type *Gs, double *S_out, double *T_out)
+{
+    const double h3 = p->g.h * p->g.h * p->g.h;
+    switch (n_iter) {
+    case 1: return launch_sums_few<T, 1>(p, want_res, h3, Gm, Gs, S_out, T_out);
+    case 2: return launch_sums_few<T, 2>(p, want_res, h3, Gm, Gs, S_out, T_out);
+    case 3: return launch_sums_few<T, 3>(p, want_res, h3, Gm, Gs, S_out, T_out);
+    case 4: return launch_sums_few<T, 4>(p, want_res, h3, Gm, Gs, S_out, T_out);
+    case 5: return launch_sums_few<T, 5>(p, want_res, h3, Gm, Gs, S_out, T_out);
+    case 6: return launch_sums_few<T, 6>(p, want_res, h3, Gm, Gs, S_out, T_out);
+    case 7: return launch_sums_few<T, 7>(p, want_res, h3, Gm, Gs, S_out, T_out);
+    case 8: return launch_sums_few<T, kFewPasses>(p, want_res, h3, Gm, Gs, S_out, T_out);
+    }
+    hipLaunchKernelGGL((k_particle_sums<T>), dim3(nblocks(p->np, 4)), dim3(256), 0, p->stream,
+                       p->np, p->nm, n_iter, want_res, h3, (const int *)p->d_moff, p->body,
+                       (const int *)p->m_inv, Gm, Gs, S_out, T_out, p->rpart);
+}
+
 template <typename T, int W>
 ibmx_status run_forcing(ibmx_plan p, T *u, T *f_tot, const double *xp, const double *up,
                         const double *wp, const uint8_t *mask, double *S_out, double *T_out,
@@ -1856,10 +1996,7 @@ ibmx_status run_forcing(ibmx_plan p, T *u, T *f_tot, const double *xp, const dou
     }
     {
         ProfScope ps(p, IBMX_K_OTHER);
-        hipLaunchKernelGGL((k_particle_sums<T>), dim3(nblocks(np, 4)), dim3(256), 0, s, np, nm,
-                           n_iter, resid_out ? 1 : 0, p->g.h * p->g.h * p->g.h,
-                           (const int *)p->d_moff, p->body, (const int *)p->m_inv,
-                           (const T4 *)rec_Gm, rec_Gs, S_out, T_out, p->rpart);
+        launch_sums<T>(p, n_iter, resid_out ? 1 : 0, (const T4 *)rec_Gm, rec_Gs, S_out, T_out);
         if (resid_out)
             hipLaunchKernelGGL(k_finish_resid, dim3(n_iter + 1), dim3(1024), 0, s,
                                (const double *)p->rpart, np, resid_out);

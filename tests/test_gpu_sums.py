@@ -1,0 +1,49 @@
+"""Particle force, torque and residual sums where their split changes: up to
+eight passes in registers or more through the general kernel, one wave per
+particle or several (by the particle count and the average marker count),
+particles without markers, with less than one wave's and with a remainder.
+
+Tolerance 1e-12 in FP64, as for every forcing output (the sums differ from the
+oracle's by their order)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2109_03972_amd import ibmx, synth
+from tests._util import rel_err, require_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("np_,marks", [(3, (0, 1, 1300)), (7, (64, 65, 130)), (511, (0, 3, 70)),
+                                       (512, (0, 3, 70)), (4095, (0, 1, 5)), (4096, (0, 1, 5))])
+@pytest.mark.parametrize("n_iter", [1, 8, 9])
+def test_particle_sums_splits(np_, marks, n_iter):
+    import torch
+    dev = require_gpu()
+    rng = np.random.default_rng(np_ + n_iter)
+    case = synth.small_case(3, n=(48, 40, 44), periodic=(1, 1, 1), diameters=(6.0,), n_iter=n_iter,
+                            disable_mode=0)
+    cnt = np.array(marks)[np.arange(np_) % len(marks)]
+    case.moff = np.concatenate([[0], np.cumsum(cnt)]).astype(np.int32)
+    nm = int(case.moff[-1])
+    case.body = rng.normal(0.0, 3.0, (3, nm))
+    case.xp = rng.random((3, np_)) * np.array(case.n)[:, None]
+    case.up, case.wp = rng.normal(0.0, 0.1, (3, np_)), rng.normal(0.0, 0.05, (3, np_))
+    # weak markers: up to three per cell overlap here, and the passes must not
+    # diverge
+    case.dV = rng.uniform(0.05, 0.2, np_)
+    case.radius, case.mass = np.full(np_, 3.0), np.ones(np_)
+    ref = oracle.forcing(case)
+    plan = ibmx.Plan.from_case(case, "f64")
+    t = lambda a: torch.as_tensor(a, device=dev).contiguous()
+    keep = t(case.body), t(case.dV)
+    plan.set_markers(*keep)
+    u, res = t(case.u0), torch.zeros(n_iter + 1, dtype=torch.float64, device=dev)
+    f = torch.zeros_like(u)
+    S, T = plan.forcing(u, f, t(case.xp), t(case.up), t(case.wp), resid=res)
+    plan.check("forcing")
+    for k, got in (("S", S), ("T", T), ("resid", res), ("f_tot", f), ("u", u)):
+        e = rel_err(got.cpu().numpy(), ref[k])
+        assert e <= 1e-12, (k, e)
+    plan.close()
