@@ -8,6 +8,7 @@
 #define IBMX_WAVE 64
 #define IBMX_RSLOTS 1024          // spread-out accumulation slots per counter
 #define IBMX_MAX_PASSES 64        // largest n_iter of a plan
+#define IBMX_KEPT_PARTNERS 32     // partners a pair search keeps per particle
 
 // ---------------------------------------------------------------------------
 // grid constants passed by value to kernels
@@ -16,6 +17,7 @@ struct GridC {
     int n[3];
     int periodic[3];
     double h;
+    double ih_exact;   // 1/h where h is a power of two, else 0
     double inv_h3;
     double origin[3];
     long long nodes;   // nx * ny * nz

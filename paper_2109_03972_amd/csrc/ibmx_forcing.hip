@@ -99,38 +99,34 @@ __device__ __forceinline__ bool marker_geometry(const GridC &g, const double *X,
 {
     bool ok = true;
     for (int a = 0; a < 3; ++a) {
-        double s = (X[a] - g.origin[a]) / g.h - Delta<W, double>::base_shift;
+        // a power-of-two spacing has an exact reciprocal: the product is the
+        // quotient bit for bit
+        double s = X[a] - g.origin[a];
+        s = (g.ih_exact != 0.0 ? s * g.ih_exact : s / g.h) - Delta<W, double>::base_shift;
         double fl = floor(s);
         t[a] = s - fl;
-        long long bb = (long long)fl - 1;
-        if (g.periodic[a]) {
-            // the 64-bit remainder only for a base outside [0, n)
-            if (bb < 0 || bb >= g.n[a]) {
-                bb %= g.n[a];
-                if (bb < 0)
-                    bb += g.n[a];
-            }
-        } else {
-            long long last = (t[a] == 0.0) ? bb + W - 2 : bb + W - 1;
-            if (bb < 0 || last > g.n[a] - 1) {
+        // a base inside [0, n) converts to 32 bits; only one outside takes the
+        // 64-bit remainder
+        const double fb = fl - 1.0;
+        if (fb >= 0.0 && fb < (double)g.n[a]) {
+            b[a] = (int)fb;
+            if (!g.periodic[a] && b[a] + (t[a] == 0.0 ? W - 2 : W - 1) > g.n[a] - 1) {
                 ok = false;
-                bb = 0;
+                b[a] = 0;
             }
+        } else if (g.periodic[a]) {
+            long long bb = (long long)fl - 1;
+            bb %= g.n[a];
+            if (bb < 0)
+                bb += g.n[a];
+            b[a] = (int)bb;
+        } else {
+            ok = false;
+            b[a] = 0;
         }
-        b[a] = (int)bb;
     }
     return ok;
 }
-
-// tile of the marker's centre node (base + 1 on every axis)
-__device__ __forceinline__ int home_tile(const GridC &g, const TileC &tc, const int *b)
-{
-    int ti[3];
-    for (int a = 0; a < 3; ++a)
-        ti[a] = tile_of(tc, a, axis_node(g, a, b[a], 1));
-    return ti[0] + tc.nt[0] * (ti[1] + tc.nt[1] * ti[2]);
-}
-
 
 template <typename T, int W>
 __device__ __forceinline__ void stencil(const GridC &g, unsigned node, const T *tt, int ix[3][W],
@@ -195,47 +191,63 @@ constexpr int SUNR = 16;  // row groups per staging step
 
 // ---------------------------------------------------------------------------
 // halo entries: a marker registers itself with every neighbouring tile its
-// support reaches (at most 7: tiles are at least W nodes wide); a last
+// support reaches (at most 7: tiles are at least W nodes wide, so that a
+// support spans at most two tiles per axis, one of them the home tile); a last
 // support node of zero weight (t == 0) does not count.
 // ---------------------------------------------------------------------------
+// Per axis the home tile and the step (in tile indices) to the other tile the
+// support reaches, 0 for none; bit m - 1 of `left` stands for the target across
+// the axes of m's bits.
+struct HaloSet {
+    int home, d[3];
+    unsigned left;
+    __device__ int count() const { return __popc(left); }
+    // the next target tile, -1 when none is left
+    __device__ int next()
+    {
+        const int m = __ffs((int)left);
+        const int t = home + ((m & 1) ? d[0] : 0) + ((m & 2) ? d[1] : 0) + ((m & 4) ? d[2] : 0);
+        const bool any = left != 0;
+        left &= left - 1;
+        return any ? t : -1;
+    }
+};
+
 template <typename T, int W>
-__device__ __forceinline__ int halo_tiles(const GridC &g, const TileC &tc, const int *b,
-                                          const T *tt, int *tgt)
+__device__ __forceinline__ HaloSet halo_tiles(const GridC &g, const TileC &tc, const int *b,
+                                              const T *tt)
 {
-    int tl[3][2], nt[3], home[3];
+    const int stride[3] = {1, tc.nt[0], tc.nt[0] * tc.nt[1]};
+    HaloSet h;
+    h.home = 0;
+    int f = 0;
     for (int a = 0; a < 3; ++a) {
         const int last = tt[a] == T(0) ? W - 2 : W - 1;
-        home[a] = tile_of(tc, a, axis_node(g, a, b[a], 1));
+        const int th = tile_of(tc, a, axis_node(g, a, b[a], 1));
         const int t0 = tile_of(tc, a, axis_node(g, a, b[a], 0));
         const int t1 = tile_of(tc, a, axis_node(g, a, b[a], last));
-        tl[a][0] = t0;
-        tl[a][1] = t1;
-        nt[a] = t1 == t0 ? 1 : 2;
+        h.home += th * stride[a];
+        h.d[a] = ((t0 != th ? t0 : t1) - th) * stride[a];
+        f |= h.d[a] != 0 ? 1 << a : 0;
     }
-    int ntg = 0;
-    for (int kz = 0; kz < nt[2]; ++kz)
-        for (int ky = 0; ky < nt[1]; ++ky)
-            for (int kx = 0; kx < nt[0]; ++kx) {
-                const int tx = tl[0][kx], ty = tl[1][ky], tz = tl[2][kz];
-                if (tx == home[0] && ty == home[1] && tz == home[2])
-                    continue;
-                tgt[ntg++] = tx + tc.nt[0] * (ty + tc.nt[1] * tz);
-            }
-    return ntg;
+    // byte f: the nonempty subsets of f's axes
+    h.left = (unsigned)(0x7F2A190807020100ull >> (8 * f)) & 0xffu;
+    return h;
 }
 
 // Wave-aggregated halo counting: adds every lane's halo tiles to count[tile]
-// (one atomic per distinct tile and round, results unused).
-__device__ __forceinline__ void halo_count_wave(const int *tgt, int ntg, int *__restrict__ count)
+// (one atomic per distinct tile and round, results unused).  The leader's key
+// is read into a scalar register, so that the loop over the groups is scalar.
+__device__ __forceinline__ void halo_count_wave(HaloSet h, int *__restrict__ count)
 {
     const int lane = threadIdx.x & (IBMX_WAVE - 1);
-    for (int k = 0; k < 7; ++k) {
-        const int key = k < ntg ? tgt[k] : -1;
+    while (__ballot(h.left != 0)) {
+        const int key = h.next();
         unsigned long long pending = __ballot(key >= 0);
         while (pending) {
             const int leader = __ffsll((long long)pending) - 1;
-            const int kk = __shfl(key, leader, IBMX_WAVE);
-            const unsigned long long m = __ballot(key == kk) & pending;
+            const int kk = __builtin_amdgcn_readlane(key, leader);
+            const unsigned long long m = __ballot(key == kk);
             if (lane == leader)
                 atomicAdd(&count[kk], __popcll(m));
             pending &= ~m;
@@ -248,8 +260,7 @@ __device__ __forceinline__ void halo_count_wave(const int *tgt, int ntg, int *__
 // positions with one atomic on cursor[tile] -- all groups at once, so the
 // atomics' round trips overlap -- and the lanes write their record index j.
 constexpr int HGROUPS = 7 * IBMX_WAVE;
-__device__ __forceinline__ void halo_emit_wave(const int *tgt, int ntg, int j,
-                                               int *__restrict__ cursor,
+__device__ __forceinline__ void halo_emit_wave(HaloSet h, int j, int *__restrict__ cursor,
                                                const int *__restrict__ halo_start,
                                                int *__restrict__ halo_list, long long cap,
                                                int *__restrict__ err, volatile int *g_key,
@@ -258,15 +269,18 @@ __device__ __forceinline__ void halo_emit_wave(const int *tgt, int ntg, int j,
     const int lane = threadIdx.x & (IBMX_WAVE - 1);
     int grp[7], rank[7];
     int ng = 0;
+#pragma unroll
     for (int k = 0; k < 7; ++k) {
-        const int key = k < ntg ? tgt[k] : -1;
         grp[k] = -1;
         rank[k] = 0;
-        unsigned long long pending = __ballot(key >= 0);
+        unsigned long long pending = __ballot(h.left != 0);
+        if (!pending)
+            continue;
+        const int key = h.next();
         while (pending) {
             const int leader = __ffsll((long long)pending) - 1;
-            const int kk = __shfl(key, leader, IBMX_WAVE);
-            const unsigned long long m = __ballot(key == kk) & pending;
+            const int kk = __builtin_amdgcn_readlane(key, leader);
+            const unsigned long long m = __ballot(key == kk);
             if (key == kk) {
                 grp[k] = ng;
                 rank[k] = __popcll(m & lanemask_lt(lane));
@@ -283,6 +297,7 @@ __device__ __forceinline__ void halo_emit_wave(const int *tgt, int ntg, int j,
         const int key = g_key[q];
         g_pos[q] = halo_start[key] + atomicAdd(&cursor[key], g_pos[q]);
     }
+#pragma unroll
     for (int k = 0; k < 7; ++k) {
         if (grp[k] < 0)
             continue;
@@ -308,8 +323,8 @@ __device__ __forceinline__ int reserve_wave(int key, int *__restrict__ cursor,
     unsigned long long pending = __ballot(key >= 0);
     while (pending) {
         const int leader = __ffsll((long long)pending) - 1;
-        const int kk = __shfl(key, leader, IBMX_WAVE);
-        const unsigned long long m = __ballot(key == kk) & pending;
+        const int kk = __builtin_amdgcn_readlane(key, leader);
+        const unsigned long long m = __ballot(key == kk);
         if (key == kk) {
             grp = ng;
             rank = __popcll(m & lanemask_lt(lane));
@@ -342,8 +357,8 @@ __global__ __launch_bounds__(256) void k_bin_count(
 {
     const int l = blockIdx.x * blockDim.x + threadIdx.x;
     const int lane = threadIdx.x & (IBMX_WAVE - 1);
-    int key = -1, ntg = 0;
-    int tgt[7];
+    int key = -1;
+    HaloSet halo = {};
     if (l < nm && (!mask || mask[l])) {
         const int p = pid_of[l];
         double X[3], t[3];
@@ -351,9 +366,9 @@ __global__ __launch_bounds__(256) void k_bin_count(
         for (int a = 0; a < 3; ++a)
             X[a] = xp[(size_t)a * np + p] + body[(size_t)a * nm + l];
         if (marker_geometry<W>(g, X, b, t)) {
-            key = home_tile(g, tc, b);
             const T tt[3] = {(T)t[0], (T)t[1], (T)t[2]};
-            ntg = halo_tiles<T, W>(g, tc, b, tt, tgt);
+            halo = halo_tiles<T, W>(g, tc, b, tt);
+            key = halo.home;
         } else {
             atomicCAS(err, 0, (int)IBMX_EDOMAIN);
         }
@@ -363,13 +378,14 @@ __global__ __launch_bounds__(256) void k_bin_count(
     unsigned long long pending = __ballot(key >= 0);
     while (pending) {
         const int leader = __ffsll((long long)pending) - 1;
-        const int kk = __shfl(key, leader, IBMX_WAVE);
+        const int kk = __builtin_amdgcn_readlane(key, leader);
         const unsigned long long m = __ballot(key == kk) & pending;
         if (lane == leader)
             atomicAdd(&tile_count[kk], __popcll(m));
         pending &= ~m;
     }
-    halo_count_wave(tgt, ntg, halo_count);
+    const int ntg = halo.count();
+    halo_count_wave(halo, halo_count);
     slot_add(count, block_sum<long long>(key >= 0 ? 1 : 0));
     slot_add(count + 2 * IBMX_RSLOTS, block_sum<long long>(ntg));
 }
@@ -398,8 +414,7 @@ __global__ __launch_bounds__(256) void k_bin_scatter(
     const int wv = threadIdx.x / IBMX_WAVE;
     const int key = l < nm ? m_key[l] : -1;
     const int dst = reserve_wave(key, tile_cursor, tile_start, s_gkey[wv], s_gpos[wv]);
-    int tgt[7];
-    int ntg = 0;
+    HaloSet halo = {};
     if (key >= 0) {
         m_inv[l] = dst;
         const int p = pid_of[l];
@@ -426,11 +441,11 @@ __global__ __launch_bounds__(256) void k_bin_scatter(
         rec_ud[dst] = ud;
         rec_src[dst] = l;
         const T tt[3] = {tn.x, tn.y, tn.z};
-        ntg = halo_tiles<T, W>(g, tc, b, tt, tgt);
+        halo = halo_tiles<T, W>(g, tc, b, tt);
     } else if (l < nm) {
         m_inv[l] = -1;
     }
-    halo_emit_wave(tgt, ntg, dst, halo_cursor, halo_start, halo_list, halo_cap, err, s_gkey[wv],
+    halo_emit_wave(halo, dst, halo_cursor, halo_start, halo_list, halo_cap, err, s_gkey[wv],
                    s_gpos[wv]);
 }
 
@@ -1891,15 +1906,15 @@ void bin_markers(ibmx_plan p, const double *xp, const double *up, const double *
         hipLaunchKernelGGL((k_bin_count<T, W>), dim3(gb), dim3(256), 0, s, p->g, tc, np, nm,
                            p->d_pid, p->body, xp, mask, p->m_key, p->tile_count, p->halo_count,
                            p->d_err, p->d_count);
-        ibmx_exclusive_scan(p->tile_count, p->tile_start, ntiles, p->scan_aux, s);
-        ibmx_exclusive_scan(p->halo_count, p->halo_start, ntiles, p->scan_aux, s);
+        ibmx_exclusive_scan2(p->tile_count, p->tile_start, p->halo_count, p->halo_start, ntiles,
+                             p->scan_aux, s);
         hipLaunchKernelGGL((k_bin_scatter<T, W>), dim3(gb), dim3(256), 0, s, p->g, tc, np, nm,
                            p->d_pid, p->body, xp, up, wp, p->dV, p->m_key, p->tile_start,
                            p->tile_cursor, rec_tn, rec_ud, p->rec_src, p->m_inv, p->halo_start,
                            p->halo_cursor, p->halo_list, p->halo_cap, p->d_err);
     } else {
-        ibmx_exclusive_scan(p->tile_count, p->tile_start, ntiles, p->scan_aux, s);
-        ibmx_exclusive_scan(p->halo_count, p->halo_start, ntiles, p->scan_aux, s);
+        ibmx_exclusive_scan2(p->tile_count, p->tile_start, p->halo_count, p->halo_start, ntiles,
+                             p->scan_aux, s);
     }
 }
 

@@ -84,6 +84,7 @@ struct ibmx_plan_s {
     int p_cell_cap;
     int *p_wcount;        // [np + 1]
     int *p_woff;          // [np + 1]
+    int *p_found;         // [np][IBMX_KEPT_PARTNERS] partners found by the search
 
     // contact workspace (pair pass and particle sub-stepping): per-particle
     // adjacency of the contact lists, history of the previous pair call
@@ -178,6 +179,9 @@ bool ibmx_fluid_grid_ok(ibmx_plan p);
 bool ibmx_fluid_ready(ibmx_plan p);
 ibmx_status ibmx_fluid_reserve(ibmx_plan p);
 void ibmx_exclusive_scan(const int *in, int *out, int n, int *aux, hipStream_t s);
+// two scans of n elements together (aux from ibmx_scan_aux_size)
+void ibmx_exclusive_scan2(const int *in0, int *out0, const int *in1, int *out1, int n, int *aux,
+                          hipStream_t s);
 void ibmx_fill_i32(int *p, int v, long long n, hipStream_t s);
 // up to eight int arrays cleared by one launch
 struct ZeroList {

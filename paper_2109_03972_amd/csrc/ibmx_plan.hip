@@ -28,7 +28,8 @@ void free_plan(ibmx_plan p)
                     p->c_deg,       p->c_off,       p->c_cur,        p->c_adj,        p->c_hist,
                     p->s_buf,       p->fl_r,        p->fl_z,        p->fl_tw[0],     p->fl_tw[1],
                     p->fl_tw[2],         p->p_cell_of, p->p_cursor,
-                    p->p_count,     p->p_off,       p->p_wcount,     p->p_woff};
+                    p->p_count,     p->p_off,       p->p_wcount,     p->p_woff,
+                    p->p_found};
     for (void *q : ptrs)
         if (q)
             (void)hipFree(q);
@@ -141,6 +142,8 @@ ibmx_status check_params(const ibmx_grid *g, const ibmx_params *prm)
         nodes *= grid->n[a];
     }
     g.h = grid->h;
+    int h_exp = 0;
+    g.ih_exact = frexp(grid->h, &h_exp) == 0.5 && isfinite(1.0 / grid->h) ? 1.0 / grid->h : 0.0;
     g.inv_h3 = 1.0 / (grid->h * grid->h * grid->h);
     g.nodes = nodes;
     g.shift[0] = 0;
@@ -173,6 +176,7 @@ ibmx_status check_params(const ibmx_grid *g, const ibmx_params *prm)
     A((void **)&p->p_off, sizeof(int) * (npz + 1));
     A((void **)&p->p_wcount, sizeof(int) * (npz + 1));
     A((void **)&p->p_woff, sizeof(int) * (npz + 1));
+    A((void **)&p->p_found, sizeof(int) * npz * IBMX_KEPT_PARTNERS);
     A((void **)&p->c_deg, sizeof(int) * (npz + 1));
     A((void **)&p->c_off, sizeof(int) * (npz + 1));
     A((void **)&p->c_cur, sizeof(int) * npz);

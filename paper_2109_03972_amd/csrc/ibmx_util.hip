@@ -44,14 +44,22 @@ __global__ void k_fill_u8(uint8_t *p, uint8_t v, long long n)
         p[i] = v;
 }
 
-// Exclusive scan of n ints in three launches: every workgroup of 256
-// threads scans its SCAN_B = 2048 elements (8 consecutive per thread) and
-// writes its total to aux; one workgroup scans the totals (out[n] receives
-// the grand total); every workgroup then adds the scanned total of the
-// workgroups before it.  With n <= SCAN_B the first launch does all.  in and
-// out may alias (every element is read before it is written, by the same
-// thread).
+// Exclusive scans of up to two arrays of n ints (array blockIdx.y) in three
+// launches: every workgroup of 256 threads scans its SCAN_B = 2048 elements (8
+// consecutive per thread) and writes its total to the array's aux; one
+// workgroup scans the totals (out[n] receives the grand total); every workgroup
+// then adds the scanned total of the workgroups before it.  With n <= SCAN_B
+// the first launch does all.  in and out may alias (every element is read
+// before it is written, by the same thread).  Both arrays of a binning or of
+// the pair and wall lists go together: a scan is all launch latency (4.5 us a
+// launch), so two at once cost what one does.
 constexpr int SCAN_T = 256, SCAN_E = 8, SCAN_B = SCAN_T * SCAN_E;
+
+struct ScanPair {
+    const int *in[2];
+    int *out[2];
+    int *aux[2];
+};
 
 __device__ __forceinline__ int wave_incl_scan(int v)
 {
@@ -84,8 +92,10 @@ __device__ __forceinline__ int block_excl_scan(int v, int *total)
     return before + incl - v;
 }
 
-__global__ __launch_bounds__(SCAN_T) void k_scan_local(const int *in, int *out, int *aux, int n)
+__global__ __launch_bounds__(SCAN_T) void k_scan_local(ScanPair sp, int has_aux, int n)
 {
+    const int *in = sp.in[blockIdx.y];
+    int *out = sp.out[blockIdx.y];
     const long long lo = (long long)blockIdx.x * SCAN_B + (long long)threadIdx.x * SCAN_E;
     int v[SCAN_E];
 #pragma unroll
@@ -104,15 +114,16 @@ __global__ __launch_bounds__(SCAN_T) void k_scan_local(const int *in, int *out, 
         run += v[k];
     }
     if (threadIdx.x == 0) {
-        if (aux)
-            aux[blockIdx.x] = total;
+        if (has_aux)
+            sp.aux[blockIdx.y][blockIdx.x] = total;
         else
             out[n] = total;
     }
 }
 
-__global__ __launch_bounds__(SCAN_T) void k_scan_aux(int *aux, int nb, int *out, int n)
+__global__ __launch_bounds__(SCAN_T) void k_scan_aux(ScanPair sp, int nb, int n)
 {
+    int *aux = sp.aux[blockIdx.y], *out = sp.out[blockIdx.y];
     int carry = 0;
     for (int b0 = 0; b0 < nb; b0 += SCAN_T) {
         const int b = b0 + threadIdx.x;
@@ -127,10 +138,12 @@ __global__ __launch_bounds__(SCAN_T) void k_scan_aux(int *aux, int nb, int *out,
         out[n] = carry;
 }
 
-__global__ __launch_bounds__(SCAN_T) void k_scan_add(int *out, const int *aux, int n)
+__global__ __launch_bounds__(SCAN_T) void k_scan_add(ScanPair sp, int n)
 {
     if (blockIdx.x == 0)
         return;
+    int *out = sp.out[blockIdx.y];
+    const int *aux = sp.aux[blockIdx.y];
     const int add = aux[blockIdx.x];
     const long long lo = (long long)blockIdx.x * SCAN_B;
     for (int k = threadIdx.x; k < SCAN_B; k += SCAN_T)
@@ -172,18 +185,25 @@ void ibmx_fill_u8(uint8_t *p, uint8_t v, long long n, hipStream_t s)
         hipLaunchKernelGGL(k_fill_u8, dim3(fill_blocks(n)), dim3(256), 0, s, p, v, n);
 }
 
-int ibmx_scan_aux_size(long long n) { return (int)((n + SCAN_B - 1) / SCAN_B) + 1; }
+// workgroup totals of two scans
+int ibmx_scan_aux_size(long long n) { return 2 * ((int)((n + SCAN_B - 1) / SCAN_B) + 1); }
+
+void ibmx_exclusive_scan2(const int *in0, int *out0, const int *in1, int *out1, int n, int *aux,
+                          hipStream_t s)
+{
+    const int nb = (n + SCAN_B - 1) / SCAN_B, arrays = out1 ? 2 : 1;
+    const ScanPair sp = {{in0, in1}, {out0, out1}, {aux, aux + nb}};
+    hipLaunchKernelGGL(k_scan_local, dim3(nb > 1 ? nb : 1, arrays), dim3(SCAN_T), 0, s, sp,
+                       nb > 1 ? 1 : 0, n);
+    if (nb <= 1)
+        return;
+    hipLaunchKernelGGL(k_scan_aux, dim3(1, arrays), dim3(SCAN_T), 0, s, sp, nb, n);
+    hipLaunchKernelGGL(k_scan_add, dim3(nb, arrays), dim3(SCAN_T), 0, s, sp, n);
+}
 
 void ibmx_exclusive_scan(const int *in, int *out, int n, int *aux, hipStream_t s)
 {
-    const int nb = (n + SCAN_B - 1) / SCAN_B;
-    if (nb <= 1) {
-        hipLaunchKernelGGL(k_scan_local, dim3(1), dim3(SCAN_T), 0, s, in, out, (int *)nullptr, n);
-        return;
-    }
-    hipLaunchKernelGGL(k_scan_local, dim3(nb), dim3(SCAN_T), 0, s, in, out, aux, n);
-    hipLaunchKernelGGL(k_scan_aux, dim3(1), dim3(SCAN_T), 0, s, aux, nb, out, n);
-    hipLaunchKernelGGL(k_scan_add, dim3(nb), dim3(SCAN_T), 0, s, out, (const int *)aux, n);
+    ibmx_exclusive_scan2(in, out, nullptr, nullptr, n, aux, s);
 }
 
 ibmx_status ibmx_launch_check()
