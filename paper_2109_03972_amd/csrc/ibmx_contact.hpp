@@ -45,7 +45,12 @@ struct PairC {
 
 __device__ __forceinline__ double wrap_pos(double x, double o, double L)
 {
-    double t = floor((x - o) / L);
+    // inside the domain the quotient's floor is 0 (a quotient of a smaller by a
+    // larger number rounds below 1): x itself, without the division
+    const double d = x - o;
+    if (d >= 0.0 && d < L)
+        return x;
+    double t = floor(d / L);
     return x - t * L;
 }
 

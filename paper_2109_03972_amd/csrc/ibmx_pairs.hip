@@ -2,14 +2,15 @@
 //
 //   cell list   uniform cells of edge >= 2 R_max + gap_cut, particles listed
 //               per cell by id (counting sort, then a per-cell sort);
-//   pair list   27-cell search, count -> exclusive scan -> emit, each
-//               particle's partners sorted by id, so the list is in (i, j)
-//               order and independent of thread scheduling;
+//   pair list   one 27-cell search that counts and keeps each particle's
+//               partners -> exclusive scan -> emit, sorted by id, so the list
+//               is in (i, j) order and independent of thread scheduling;
 //   wall list   (p, side) for every wall closer than gap_cut;
 //   forces      lubrication, normal contact (linear or Hertz) and capped
 //               tangential spring-dashpot (eq. f_int): a group of lanes per
 //               particle evaluates its contacts, summed in partner order;
-//   mask        the marker-disable rule, one workgroup per close pair/wall.
+//   mask        the marker-disable rule, a wave per particle over its close
+//               pairs and walls.
 //
 // Distances, gaps and cell indices are computed with the operation order
 // documented in ibmx.h and without FMA contraction so that the integer
@@ -65,8 +66,7 @@ __global__ void k_cell_scatter(int np, const int *cell_of, const int *start, int
     cellp[pos] = p;
 }
 
-// insertion sort of one segment (segments are short: particles per cell,
-// partners per particle)
+// insertion sort of one segment (more partners than a search keeps)
 __device__ void sort_segment(int *a, int n)
 {
     for (int i = 1; i < n; ++i) {
@@ -80,37 +80,47 @@ __device__ void sort_segment(int *a, int n)
     }
 }
 
-__global__ void k_cell_sort(int ncell, const int *start, int *cellp)
+// a cell's particles by id: every particle counts the smaller ids of its cell
+// (independent reads; an insertion sort per cell was a chain of memory round
+// trips, 29 us on the 20,000-particle bed)
+__global__ void k_cell_sort(int np, const int *cell_of, const int *start, const int *unsorted,
+                            int *cellp)
 {
-    int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= ncell)
+    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= np)
         return;
-    sort_segment(cellp + start[c], start[c + 1] - start[c]);
+    const int c = cell_of[p], s0 = start[c], s1 = start[c + 1];
+    int rank = 0;
+    for (int k = s0; k < s1; ++k)
+        rank += unsorted[k] < p ? 1 : 0;
+    cellp[s0 + rank] = p;
 }
 
 // ---------------------------------------------------------------------------
 // pair search over the neighbouring cells (deduplicated when nc < 3), one
-// wave per particle i: the candidates of the (up to 27) cells are numbered
-// 0 .. total-1 through a wave prefix sum of the cell sizes and dealt to the
-// lanes; hits j > i are counted (EMIT = false) or written in candidate order
-// to the scratch half of pairs_out, then sorted and completed by lane 0.
+// wave per particle i.  The neighbours along x of one (y, z) row of cells are
+// one range of the cell list (two across a seam), so there are 9 to 18 ranges;
+// their candidates are numbered 0 .. total-1 through a wave prefix sum and
+// dealt to the lanes, kSearch rounds of 64 at a time with their loads in flight
+// together; visit(hit, j) is called for every 64 candidates, by the whole wave,
+// with hit = a partner j > i closer than the cut-off.  What bounds it is the
+// search of a candidate's range (27 cells' ranges read through the LDS crossbar,
+// one round at a time, took 53 us on the 20,000-particle bed; 31 now).
 // ---------------------------------------------------------------------------
-template <bool EMIT>
-__global__ __launch_bounds__(256) void k_pairs(PairC P, int np, const double *xp,
-                                               const double *radius, const int *cell_start,
-                                               const int *cellp, int *count, const int *off,
-                                               int cap, int *pairs_out, double *gap_out)
+constexpr int kSearch = 2;
+
+template <class Visit>
+__device__ __forceinline__ void search_partners(const PairC &P, int np, const double *xp,
+                                                const double *radius, const int *cell_start,
+                                                const int *cellp, int i, const double *xi,
+                                                double Ri, Visit visit)
 {
     const int lane = threadIdx.x & (IBMX_WAVE - 1);
-    const int i = blockIdx.x * (blockDim.x / IBMX_WAVE) + threadIdx.x / IBMX_WAVE;
-    if (i >= np)
-        return;
-    double xi[3];
     int ci[3];
-    centre(P, np, xp, i, xi);
     cell_coords(P, xi, ci);
+    // cell rows along y and z (deduplicated)
     int offs[3][3], noff[3];
-    for (int a = 0; a < 3; ++a) {
+    for (int a = 1; a < 3; ++a) {
         noff[a] = 0;
         for (int d = -1; d <= 1; ++d) {
             int v = ci[a] + d;
@@ -126,119 +136,202 @@ __global__ __launch_bounds__(256) void k_pairs(PairC P, int np, const double *xp
                 offs[a][noff[a]++] = v;
         }
     }
-    const int ncells = noff[0] * noff[1] * noff[2];
-    // lane k < ncells holds cell k's range and the number of candidates before it
+    // ranges of cells along x: [x0, x1], across a seam also the single cell xs
+    const int nx = P.nc[0];
+    int x0 = max(ci[0] - 1, 0), x1 = min(ci[0] + 1, nx - 1), xs = -1;
+    if (P.periodic[0] && nx > 3) {
+        if (ci[0] == 0)
+            xs = nx - 1;
+        else if (ci[0] == nx - 1)
+            xs = 0;
+    } else if (P.periodic[0]) {
+        x0 = 0, x1 = nx - 1;   // every cell is a neighbour
+    }
+    const int nxr = xs >= 0 ? 2 : 1;
+    const int nranges = __builtin_amdgcn_readfirstlane(nxr * noff[1] * noff[2]);
+    // lane k < nranges holds range k and the number of candidates before it
     int c_first = 0, c_len = 0;
-    if (lane < ncells) {
-        const int kx = lane % noff[0], ky = (lane / noff[0]) % noff[1], kz = lane / (noff[0] * noff[1]);
-        const int c = offs[0][kx] + P.nc[0] * (offs[1][ky] + P.nc[1] * offs[2][kz]);
-        c_first = cell_start[c];
-        c_len = cell_start[c + 1] - c_first;
+    if (lane < nranges) {
+        const int kx = lane % nxr, ky = (lane / nxr) % noff[1], kz = lane / (nxr * noff[1]);
+        const int row = nx * (offs[1][ky] + P.nc[1] * offs[2][kz]);
+        c_first = cell_start[row + (kx == 0 ? x0 : xs)];
+        c_len = cell_start[row + (kx == 0 ? x1 : xs) + 1] - c_first;
     }
     int c_pre = c_len;   // inclusive wave scan
-    for (int d = 1; d < IBMX_WAVE; d <<= 1) {
+    for (int d = 1; d < IBMX_WAVE / 2; d <<= 1) {
         const int v = __shfl_up(c_pre, d, IBMX_WAVE);
         if (lane >= d)
             c_pre += v;
     }
-    const int total = __shfl(c_pre, IBMX_WAVE - 1, IBMX_WAVE);
+    const int total = __builtin_amdgcn_readlane(c_pre, nranges - 1);
     c_pre -= c_len;   // exclusive
-    const double Ri = radius[i];
-    const int base = EMIT ? off[i] : 0;
-    int cnt = 0;
-    for (int t0 = 0; t0 < total; t0 += IBMX_WAVE) {
-        const int t = t0 + lane;
-        // the cell k holding candidate t: the last k with c_pre[k] <= t
-        int first = 0, pre = 0;
-        for (int k = 0; k < ncells; ++k) {
-            const int pk = __shfl(c_pre, k, IBMX_WAVE);
-            const int fk = __shfl(c_first, k, IBMX_WAVE);
-            if (pk <= t) {
-                pre = pk;
-                first = fk;
+    for (int t0 = 0; t0 < total; t0 += kSearch * IBMX_WAVE) {
+        // the range k holding candidate t: the last k with c_pre[k] <= t
+        int at[kSearch], j[kSearch];
+        for (int k = 0; k < nranges; ++k) {
+            const int pk = __builtin_amdgcn_readlane(c_pre, k);
+            const int fk = __builtin_amdgcn_readlane(c_first, k) - pk;
+#pragma unroll
+            for (int q = 0; q < kSearch; ++q) {
+                const int t = t0 + q * IBMX_WAVE + lane;
+                at[q] = pk <= t ? fk + t : at[q];
             }
         }
-        bool hit = false;
-        int j = -1;
-        if (t < total) {
-            j = cellp[first + (t - pre)];
-            if (j > i) {
-                double xj[3], d[3];
-                centre(P, np, xp, j, xj);
-                const double d2 = disp2(P, xi, xj, d);
-                double cut = Ri + radius[j];
+#pragma unroll
+        for (int q = 0; q < kSearch; ++q)
+            j[q] = cellp[t0 + q * IBMX_WAVE + lane < total ? at[q] : 0];
+        double xj[kSearch][3], Rj[kSearch];
+#pragma unroll
+        for (int q = 0; q < kSearch; ++q) {
+            for (int a = 0; a < 3; ++a)
+                xj[q][a] = xp[(size_t)a * np + j[q]];
+            Rj[q] = radius[j[q]];
+        }
+#pragma unroll
+        for (int q = 0; q < kSearch; ++q) {
+            bool hit = false;
+            if (t0 + q * IBMX_WAVE + lane < total && j[q] > i) {
+                double d[3];
+                for (int a = 0; a < 3; ++a)
+                    if (P.periodic[a])
+                        xj[q][a] = wrap_pos(xj[q][a], P.origin[a], P.L[a]);
+                const double d2 = disp2(P, xi, xj[q], d);
+                double cut = Ri + Rj[q];
                 cut = cut + P.gap_cut;
                 hit = d2 < cut * cut;
             }
+            visit(hit, j[q]);
         }
+    }
+}
+
+// Search and counts: the first kKept partners of every particle are kept
+// (found[i][kKept], in search order) and its walls counted by the wave's first
+// six lanes, so that the lists need no second search.
+constexpr int kKept = IBMX_KEPT_PARTNERS;
+
+// gap of particle p to wall `side` (2 axis + upper); true when it is listed
+__device__ __forceinline__ bool wall_gap_of(const PairC &P, int np, const double *xp, double R,
+                                            int p, int side, double *g)
+{
+    bool in = false;
+    for (int a = 0; a < 3; ++a) {
+        if (P.periodic[a] || side / 2 != a)
+            continue;
+        const double x = xp[(size_t)a * np + p];
+        const double top = P.origin[a] + P.L[a];
+        const double dist = (side & 1) == 0 ? (x - P.origin[a]) : (top - x);
+        *g = dist - R;
+        in = *g < P.gap_cut;
+    }
+    return in;
+}
+
+__global__ __launch_bounds__(256) void k_pairs_count(PairC P, int np, const double *xp,
+                                                     const double *radius, const int *cell_start,
+                                                     const int *cellp, int *count, int *wcount,
+                                                     int *found)
+{
+    const int lane = threadIdx.x & (IBMX_WAVE - 1);
+    const int i = blockIdx.x * (blockDim.x / IBMX_WAVE) +
+                  __builtin_amdgcn_readfirstlane(threadIdx.x / IBMX_WAVE);
+    if (i >= np)
+        return;
+    double xi[3];
+    centre(P, np, xp, i, xi);
+    const double Ri = radius[i];
+    int cnt = 0;
+    search_partners(P, np, xp, radius, cell_start, cellp, i, xi, Ri, [&](bool hit, int j) {
         const unsigned long long m = __ballot(hit);
-        if (EMIT && hit) {
-            const int pos = cnt + __popcll(m & ((1ULL << lane) - 1ULL));
-            if (base + pos < cap)
-                pairs_out[cap + base + pos] = j;   // partner ids, sorted below
-        }
+        const int pos = cnt + __popcll(m & ((1ULL << lane) - 1ULL));
+        if (hit && pos < kKept)
+            found[(size_t)i * kKept + pos] = j;
         cnt += __popcll(m);
+    });
+    double g = 0.0;
+    const bool wall = lane < 6 && wall_gap_of(P, np, xp, Ri, i, lane, &g);
+    const int nw = __popcll(__ballot(wall));
+    if (lane == 0) {
+        count[i] = cnt;
+        wcount[i] = nw;
     }
-    if (!EMIT) {
-        if (lane == 0)
-            count[i] = cnt;
-        return;
+}
+
+// The lists: a wave per particle orders its kept partners by id (each lane
+// counts the smaller ones) and writes them with their gaps, then its walls; a
+// particle with more partners than were kept searches again.  The first wave
+// also writes the totals.
+__global__ __launch_bounds__(256) void k_pairs_emit(PairC P, int np, const double *xp,
+                                                    const double *radius, const int *cell_start,
+                                                    const int *cellp, const int *found,
+                                                    const int *off, int cap, int *pairs_out,
+                                                    double *gap_out, const int *woff, int wcap,
+                                                    int *walls_out, double *wgap_out,
+                                                    int *counts_out, int *err)
+{
+    const int lane = threadIdx.x & (IBMX_WAVE - 1);
+    const int i = blockIdx.x * (blockDim.x / IBMX_WAVE) +
+                  __builtin_amdgcn_readfirstlane(threadIdx.x / IBMX_WAVE);
+    if (i == 0 && lane == 0) {
+        counts_out[0] = off[np];
+        counts_out[1] = woff[np];
+        if (off[np] > cap || woff[np] > wcap)
+            atomicCAS(err, 0, (int)IBMX_ECAPACITY);
     }
-    // sort the partners of i, then write i and the gaps in that order
-    const int n = min(cnt, cap - base);
-    if (n <= 0 || lane != 0)
+    if (i >= np)
         return;
-    sort_segment(pairs_out + cap + base, n);
-    for (int k = 0; k < n; ++k) {
-        int j = pairs_out[cap + base + k];
+    double xi[3];
+    centre(P, np, xp, i, xi);
+    const double Ri = radius[i];
+    const int base = off[i], cnt = off[i + 1] - base;
+    auto gap_to = [&](int j) {
         double xj[3], d[3];
         centre(P, np, xp, j, xj);
         double d2 = disp2(P, xi, xj, d);
-        pairs_out[base + k] = i;
         double g = sqrt(d2) - Ri;
-        gap_out[base + k] = g - radius[j];
-    }
-}
-
-template <bool EMIT>
-__global__ void k_walls(PairC P, int np, const double *xp, const double *radius, int *count,
-                        const int *off, int cap, int *walls_out, double *gap_out)
-{
-    int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= np)
-        return;
-    int cnt = 0;
-    const int base = EMIT ? off[p] : 0;
-    for (int a = 0; a < 3; ++a) {
-        if (P.periodic[a])
-            continue;
-        double x = xp[(size_t)a * np + p];
-        for (int side = 0; side < 2; ++side) {
-            double top = P.origin[a] + P.L[a];
-            double dist = side == 0 ? (x - P.origin[a]) : (top - x);
-            double g = dist - radius[p];
-            if (g < P.gap_cut) {
-                if (EMIT && base + cnt < cap) {
-                    walls_out[base + cnt] = p;
-                    walls_out[cap + base + cnt] = 2 * a + side;
-                    gap_out[base + cnt] = g;
-                }
-                ++cnt;
+        return g - radius[j];
+    };
+    if (cnt > 0 && cnt <= kKept) {
+        const int j = lane < cnt ? found[(size_t)i * kKept + lane] : -1;
+        int rank = 0;
+        for (int k = 0; k < cnt; ++k)
+            rank += __builtin_amdgcn_readlane(j, k) < j ? 1 : 0;
+        const int pos = base + rank;
+        if (lane < cnt && pos < cap) {
+            pairs_out[pos] = i;
+            pairs_out[cap + pos] = j;
+            gap_out[pos] = gap_to(j);
+        }
+    } else if (cnt > kKept) {
+        // searched again, in candidate order into the scratch half of pairs_out,
+        // then sorted and completed by lane 0
+        int at = 0;
+        search_partners(P, np, xp, radius, cell_start, cellp, i, xi, Ri, [&](bool hit, int j) {
+            const unsigned long long m = __ballot(hit);
+            const int pos = base + at + __popcll(m & ((1ULL << lane) - 1ULL));
+            if (hit && pos < cap)
+                pairs_out[cap + pos] = j;
+            at += __popcll(m);
+        });
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        const int n = min(cnt, cap - base);
+        if (n > 0 && lane == 0) {
+            sort_segment(pairs_out + cap + base, n);
+            for (int k = 0; k < n; ++k) {
+                pairs_out[base + k] = i;
+                gap_out[base + k] = gap_to(pairs_out[cap + base + k]);
             }
         }
     }
-    if (!EMIT)
-        count[p] = cnt;
-}
-
-__global__ void k_list_totals(const int *poff, const int *woff, int np, int pair_cap, int wall_cap,
-                              int *counts_out, int *err)
-{
-    int np_ = poff[np], nw = woff[np];
-    counts_out[0] = np_;
-    counts_out[1] = nw;
-    if (np_ > pair_cap || nw > wall_cap)
-        atomicCAS(err, 0, (int)IBMX_ECAPACITY);
+    double g = 0.0;
+    const bool wall = lane < 6 && wall_gap_of(P, np, xp, Ri, i, lane, &g);
+    const unsigned long long m = __ballot(wall);
+    const int pos = woff[i] + __popcll(m & ((1ULL << lane) - 1ULL));
+    if (wall && pos < wcap) {
+        walls_out[pos] = i;
+        walls_out[wcap + pos] = lane;
+        wgap_out[pos] = g;
+    }
 }
 
 // previous-call history of pair (i, j): binary search in the (i, j)-sorted list
@@ -314,106 +407,128 @@ __device__ __forceinline__ unsigned long long splitmix64(unsigned long long x)
     return z ^ (z >> 31);
 }
 
-// one wave per pair (wall entry); lanes take the chosen particle's markers
-constexpr int MUNR = 8;   // marker rounds per batch of offset loads in the mask kernels
+// One wave per particle writes its markers' mask: 1, or 0 where the rule drops
+// the marker.  The particle's close pairs in which it is the chosen one (from
+// its adjacency, kMaskPart at a time in LDS) and its close walls are gathered
+// first, so that the marker offsets are read once, and only where there are
+// any; MUNR rounds of them are loaded before any test (four at five waves per
+// SIMD: eight took 195 VGPRs and 83 us).  20,000-particle bed: 41 us against 56
+// for clearing the mask and a wave per pair and per wall.
+constexpr int MUNR = 4;        // marker rounds per batch of offset loads
+constexpr int kMaskPart = IBMX_WAVE;
 
-__global__ __launch_bounds__(256) void k_mask_pairs(PairC P, int np, int nm, const int *moff,
-                                                    const double *body, const double *xp,
-                                                    const double *radius, int mode,
-                                                    unsigned long long seed, const int *counts,
-                                                    int cap, const int *pairs, const double *gap,
-                                                    uint8_t *mask)
+__global__ __launch_bounds__(256, 5) void k_mask(PairC P, int np, int nm, const int *moff,
+                                              const double *body, const double *xp,
+                                              const double *radius, int mode,
+                                              unsigned long long seed, const int *off,
+                                              const int2 *adj, const double *gap,
+                                              const double *wgap, uint8_t *mask)
 {
-    const int npairs = min(counts[0], cap);
+    __shared__ double part[4][kMaskPart][4];
     const int lane = threadIdx.x & (IBMX_WAVE - 1);
-    const int wpb = blockDim.x / IBMX_WAVE;
-    for (int k = blockIdx.x * wpb + threadIdx.x / IBMX_WAVE; k < npairs; k += gridDim.x * wpb) {
-        if (!(gap[k] < 2.0 * P.eps_sep))
-            continue;
-        int p = pairs[k], q = pairs[cap + k];
-        unsigned long long key =
-            ((unsigned long long)(unsigned)p << 32) | (unsigned long long)(unsigned)q;
-        int chosen = (splitmix64(seed ^ key) & 1ULL) == 0 ? p : q;
-        int partner = chosen == p ? q : p;
-        double xc[3], xq[3];
-        centre(P, np, xp, chosen, xc);
-        centre(P, np, xp, partner, xq);
-        double lim = radius[partner] + 2.0 * P.eps_sep;
-        double lim2 = lim * lim;
-        const int l1 = moff[chosen + 1];
-        if (mode == 2) {
-            for (int l = moff[chosen] + lane; l < l1; l += IBMX_WAVE)
-                mask[l] = 0;
-            continue;
-        }
-        // MUNR rounds of offsets loaded before any test, so that a large
-        // particle's markers cost few memory round trips
-        for (int l0 = moff[chosen] + lane; l0 < l1; l0 += MUNR * IBMX_WAVE) {
-            double o[MUNR][3];
-#pragma unroll
-            for (int r = 0; r < MUNR; ++r) {
-                const int l = l0 + r * IBMX_WAVE;
-#pragma unroll
-                for (int a = 0; a < 3; ++a)
-                    o[r][a] = l < l1 ? body[(size_t)a * nm + l] : 0.0;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / IBMX_WAVE);
+    const int p = blockIdx.x * 4 + wv;
+    if (p >= np)
+        return;
+    const int l0 = moff[p], l1 = moff[p + 1], e0 = off[p], e1 = off[p + 1];
+    double xc[3], xw[3];
+    centre(P, np, xp, p, xc);
+    for (int a = 0; a < 3; ++a)
+        xw[a] = xp[(size_t)a * np + p];
+    bool first = true;
+    for (int eb = e0; eb < e1 || first; eb += kMaskPart) {
+        // this chunk's partners whose surface drops markers, and walls
+        int q = -1, side = -1;
+        if (eb + lane < e1) {
+            const int2 e = adj[eb + lane];
+            if (e.x >= 0) {
+                const int i = (e.x & 1) ? e.y : p, j = (e.x & 1) ? p : e.y;
+                const unsigned long long key =
+                    ((unsigned long long)(unsigned)i << 32) | (unsigned long long)(unsigned)j;
+                const int chosen = (splitmix64(seed ^ key) & 1ULL) == 0 ? i : j;
+                if (chosen == p && gap[e.x >> 1] < 2.0 * P.eps_sep)
+                    q = e.y;
+            } else if (wgap[-e.x - 1] < P.eps_sep) {
+                side = e.y;
             }
+        }
+        const unsigned long long mq = __ballot(q >= 0);
+        const int nq = __popcll(mq);
+        if (q >= 0) {
+            double xq[3];
+            centre(P, np, xp, q, xq);
+            const double lim = radius[q] + 2.0 * P.eps_sep;
+            double *d = part[wv][__popcll(mq & ((1ULL << lane) - 1ULL))];
+            d[0] = xq[0];
+            d[1] = xq[1];
+            d[2] = xq[2];
+            d[3] = lim * lim;
+        }
+        bool near[6];
+        bool walls = false;
+        for (int w = 0; w < 6; ++w) {
+            near[w] = __ballot(side == w) != 0;
+            walls |= near[w];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (nq == 0 && !walls) {
+            if (first)
+                for (int l = l0 + lane; l < l1; l += IBMX_WAVE)
+                    mask[l] = 1;
+        } else if (mode == 2) {
+            for (int l = l0 + lane; l < l1; l += IBMX_WAVE)
+                mask[l] = 0;
+        } else {
+            for (int lb = l0 + lane; lb < l1; lb += MUNR * IBMX_WAVE) {
+                double o[MUNR][3];
+                bool drop[MUNR];
 #pragma unroll
-            for (int r = 0; r < MUNR; ++r) {
-                const int l = l0 + r * IBMX_WAVE;
-                double d[3];
+                for (int r = 0; r < MUNR; ++r) {
+                    const int l = min(lb + r * IBMX_WAVE, l1 - 1);
 #pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    d[a] = (xc[a] + o[r][a]) - xq[a];
-                    if (P.periodic[a])
-                        d[a] = min_image(d[a], P.L[a]);
+                    for (int a = 0; a < 3; ++a)
+                        o[r][a] = body[(size_t)a * nm + l];
+                    drop[r] = false;
                 }
-                double d2 = d[0] * d[0];
-                d2 = d2 + d[1] * d[1];
-                d2 = d2 + d[2] * d[2];
-                if (l < l1 && d2 < lim2)
-                    mask[l] = 0;
-            }
-        }
-    }
-}
-
-__global__ __launch_bounds__(256) void k_mask_walls(PairC P, int np, int nm, const int *moff,
-                                                    const double *body, const double *xp, int mode,
-                                                    const int *counts, int cap, const int *walls,
-                                                    const double *wgap, uint8_t *mask)
-{
-    const int nwall = min(counts[1], cap);
-    const int lane = threadIdx.x & (IBMX_WAVE - 1);
-    const int wpb = blockDim.x / IBMX_WAVE;
-    for (int k = blockIdx.x * wpb + threadIdx.x / IBMX_WAVE; k < nwall; k += gridDim.x * wpb) {
-        if (!(wgap[k] < P.eps_sep))
-            continue;
-        int p = walls[k], side = walls[cap + k];
-        int ax = side / 2, upper = side % 2;
-        double top = P.origin[ax] + P.L[ax];
-        const int l1 = moff[p + 1];
-        if (mode == 2) {
-            for (int l = moff[p] + lane; l < l1; l += IBMX_WAVE)
-                mask[l] = 0;
-            continue;
-        }
-        const double xa = xp[(size_t)ax * np + p];
-        for (int l0 = moff[p] + lane; l0 < l1; l0 += MUNR * IBMX_WAVE) {
-            double o[MUNR];
+                for (int k = 0; k < nq; ++k) {
+                    const double *xq = part[wv][k];
 #pragma unroll
-            for (int r = 0; r < MUNR; ++r) {
-                const int l = l0 + r * IBMX_WAVE;
-                o[r] = l < l1 ? body[(size_t)ax * nm + l] : 0.0;
-            }
+                    for (int r = 0; r < MUNR; ++r) {
+                        double d[3];
 #pragma unroll
-            for (int r = 0; r < MUNR; ++r) {
-                const int l = l0 + r * IBMX_WAVE;
-                double X = xa + o[r];
-                double dist = upper == 0 ? (X - P.origin[ax]) : (top - X);
-                if (l < l1 && dist < P.eps_sep)
-                    mask[l] = 0;
+                        for (int a = 0; a < 3; ++a) {
+                            d[a] = (xc[a] + o[r][a]) - xq[a];
+                            if (P.periodic[a])
+                                d[a] = min_image(d[a], P.L[a]);
+                        }
+                        double d2 = d[0] * d[0];
+                        d2 = d2 + d[1] * d[1];
+                        d2 = d2 + d[2] * d[2];
+                        drop[r] |= d2 < xq[3];
+                    }
+                }
+                if (walls)
+                    for (int a = 0; a < 3; ++a) {
+                        const double top = P.origin[a] + P.L[a];
+#pragma unroll
+                        for (int r = 0; r < MUNR; ++r) {
+                            const double X = xw[a] + o[r][a];
+                            drop[r] |= near[2 * a] && X - P.origin[a] < P.eps_sep;
+                            drop[r] |= near[2 * a + 1] && top - X < P.eps_sep;
+                        }
+                    }
+#pragma unroll
+                for (int r = 0; r < MUNR; ++r) {
+                    const int l = lb + r * IBMX_WAVE;
+                    if (l < l1 && (first || drop[r]))
+                        mask[l] = drop[r] ? 0 : 1;
+                }
             }
         }
+        first = false;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -475,28 +590,23 @@ extern "C" ibmx_status ibmx_pairs(ibmx_plan p, const double *xp, const double *r
                            rmax, p->p_cell_of, cell_start, p->d_err);
     ibmx_exclusive_scan(cell_start, cell_start, (int)ncell, p->scan_aux, s);
     if (np > 0) {
+        // p_off holds the unsorted cell list until the scan writes it
         hipLaunchKernelGGL(k_cell_scatter, dim3(blocks(np)), dim3(256), 0, s, np, p->p_cell_of,
-                           cell_start, p->p_cursor, cell_particles);
-        hipLaunchKernelGGL(k_cell_sort, dim3(blocks(ncell)), dim3(256), 0, s, (int)ncell,
-                           cell_start, cell_particles);
+                           cell_start, p->p_cursor, p->p_off);
+        hipLaunchKernelGGL(k_cell_sort, dim3(blocks(np)), dim3(256), 0, s, np,
+                           (const int *)p->p_cell_of, (const int *)cell_start,
+                           (const int *)p->p_off, cell_particles);
         // pair and wall lists
-        hipLaunchKernelGGL(k_pairs<false>, dim3(blocks(np, 4)), dim3(256), 0, s, P, np, xp, radius,
-                           cell_start, cell_particles, p->p_count, (const int *)nullptr, 0,
-                           (int *)nullptr, (double *)nullptr);
-        hipLaunchKernelGGL(k_walls<false>, dim3(blocks(np)), dim3(256), 0, s, P, np, xp, radius,
-                           p->p_wcount, (const int *)nullptr, 0, (int *)nullptr, (double *)nullptr);
+        hipLaunchKernelGGL(k_pairs_count, dim3(blocks(np, 4)), dim3(256), 0, s, P, np, xp, radius,
+                           (const int *)cell_start, (const int *)cell_particles, p->p_count,
+                           p->p_wcount, p->p_found);
     }
-    ibmx_exclusive_scan(p->p_count, p->p_off, np, p->scan_aux, s);
-    ibmx_exclusive_scan(p->p_wcount, p->p_woff, np, p->scan_aux, s);
-    if (np > 0) {
-        hipLaunchKernelGGL(k_pairs<true>, dim3(blocks(np, 4)), dim3(256), 0, s, P, np, xp, radius,
-                           cell_start, cell_particles, p->p_count, p->p_off, pair_cap, pairs_out,
-                           pair_gap);
-        hipLaunchKernelGGL(k_walls<true>, dim3(blocks(np)), dim3(256), 0, s, P, np, xp, radius,
-                           p->p_wcount, p->p_woff, wall_cap, walls_out, wall_gap);
-    }
-    hipLaunchKernelGGL(k_list_totals, dim3(1), dim3(1), 0, s, p->p_off, p->p_woff, np, pair_cap,
-                       wall_cap, counts_out, p->d_err);
+    ibmx_exclusive_scan2(p->p_count, p->p_off, p->p_wcount, p->p_woff, np, p->scan_aux, s);
+    hipLaunchKernelGGL(k_pairs_emit, dim3(blocks(np, 4)), dim3(256), 0, s, P, np, xp, radius,
+                       (const int *)cell_start, (const int *)cell_particles,
+                       (const int *)p->p_found, (const int *)p->p_off, pair_cap, pairs_out,
+                       pair_gap, (const int *)p->p_woff, wall_cap, walls_out, wall_gap, counts_out,
+                       p->d_err);
     // forces: previous history aligned with the new lists, per-particle
     // adjacency, then one thread per particle
     const ContactLists C{pair_cap, wall_cap, pairs_out, walls_out, counts_out};
@@ -520,20 +630,14 @@ extern "C" ibmx_status ibmx_pairs(ibmx_plan p, const double *xp, const double *r
                                 Stage{}, s);
     // mask
     if (marker_active && nm > 0) {
-        ibmx_fill_u8(marker_active, 1, nm, s);
-        if (prm.disable_mode != 0) {
-            if (pair_cap > 0)
-                hipLaunchKernelGGL(k_mask_pairs, dim3(min(blocks(pair_cap, 4), 8192)), dim3(256), 0, s,
-                                   P, np, nm,
-                                   p->d_moff, p->body, xp, radius, prm.disable_mode,
-                                   (unsigned long long)prm.disable_seed, counts_out, pair_cap,
-                                   pairs_out, pair_gap, marker_active);
-            if (wall_cap > 0)
-                hipLaunchKernelGGL(k_mask_walls, dim3(min(blocks(wall_cap, 4), 8192)), dim3(256), 0, s,
-                                   P, np, nm,
-                                   p->d_moff, p->body, xp, prm.disable_mode, counts_out, wall_cap,
-                                   walls_out, wall_gap, marker_active);
-        }
+        if (prm.disable_mode == 0)
+            ibmx_fill_u8(marker_active, 1, nm, s);
+        else
+            hipLaunchKernelGGL(k_mask, dim3(blocks(np, 4)), dim3(256), 0, s, P, np, nm,
+                               (const int *)p->d_moff, p->body, xp, radius, prm.disable_mode,
+                               (unsigned long long)prm.disable_seed, (const int *)p->c_off,
+                               (const int2 *)p->c_adj, (const double *)pair_gap,
+                               (const double *)wall_gap, marker_active);
     }
     return ibmx_launch_check();
 }
