@@ -31,6 +31,7 @@ struct FluidC {
     int n[3];
     int periodic[3];
     double h, c, nu, theta;
+    int planes;                // planes per run of a stencil column
     double ih, ih2, i2h, ic;   // 1/h, 1/h^2, 1/(2h), 1/c: the stencils multiply
 };
 
@@ -60,7 +61,7 @@ __device__ __forceinline__ const T &fat(const T *base, unsigned i)
 }
 
 // Stencil kernels that need neighbours in all three axes march a PX x PY
-// column of cells up in z over a run of kPlanes planes.  The fields' planes,
+// column of cells up in z over a run of F.planes planes.  The fields' planes,
 // with a one-cell rim for the x and y neighbours, pass through a ring of
 // kRing planes in LDS: plane k + 1 is stored, then, while plane k is
 // computed from planes k - 1, k and k + 1, plane k + 2 is loaded into
@@ -68,7 +69,7 @@ __device__ __forceinline__ const T &fat(const T *base, unsigned i)
 // plane at each end).  With four slots the store of plane k + 1 cannot meet
 // a read of the slot it reuses (last read while computing plane k - 2), so
 // one barrier per plane suffices.
-constexpr int PX = 64, PY = 4, kPlanes = 32, kRing = 4;
+constexpr int PX = 64, PY = 4, kRing = 4;
 
 // plane above / below kk, -1 behind a wall
 __device__ __forceinline__ int z_up(const FluidC &F, int kk)
@@ -88,7 +89,7 @@ struct Column {
     {
         tx = threadIdx.x % PX, ty = threadIdx.x / PX;
         i0 = blockIdx.x * PX, j0 = blockIdx.y * PY;
-        k0 = blockIdx.z * kPlanes, k1 = min(F.n[2], k0 + kPlanes);
+        k0 = blockIdx.z * F.planes, k1 = min(F.n[2], k0 + F.planes);
         i = i0 + tx, j = j0 + ty;
         live = i < F.n[0] && j < F.n[1];
         in_m[0] = F.periodic[0] || i > 0, in_p[0] = F.periodic[0] || i + 1 < F.n[0];
@@ -162,7 +163,20 @@ __device__ __forceinline__ T ring_nb(const T (*ring)[NF][PY + 2][PX + 2], const 
 
 dim3 column_grid(const FluidC &F)
 {
-    return dim3((F.n[0] + PX - 1) / PX, (F.n[1] + PY - 1) / PY, (F.n[2] + kPlanes - 1) / kPlanes);
+    return dim3((F.n[0] + PX - 1) / PX, (F.n[1] + PY - 1) / PY, (F.n[2] + F.planes - 1) / F.planes);
+}
+
+// Planes per run: 32 (a run re-reads two planes), fewer while that leaves less
+// than eight workgroups per CU, down to 4.  On 128^3, FP64, 32 planes are one
+// workgroup per CU: predictor 80 us, correction 55, against 70 and 45 with 4
+// (the face divergence, 33, does not care); on 512^3 16, 32 and 64 take the same.
+int column_planes(const int *n)
+{
+    const long long cols = (long long)((n[0] + PX - 1) / PX) * ((n[1] + PY - 1) / PY);
+    int planes = 32;
+    while (planes > 4 && cols * ((n[2] + planes - 1) / planes) < 2048)
+        planes /= 2;
+    return planes;
 }
 
 // u_f* = mean of the two cells of each +a face (wall faces 0), and the
@@ -1150,6 +1164,7 @@ FluidC fluid_constants(const ibmx_plan p, double theta)
         F.n[a] = g.n[a];
         F.periodic[a] = g.periodic[a];
     }
+    F.planes = column_planes(F.n);
     F.h = g.h;
     F.ih = 1.0 / g.h;
     F.ih2 = 1.0 / (g.h * g.h);
