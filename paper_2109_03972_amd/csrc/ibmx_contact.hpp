@@ -94,6 +94,51 @@ __device__ __forceinline__ double kn_grav(const PairC &P, double m, double R)
     return m * P.g_abs / (a * sqrt(a));
 }
 
+// What a contact's two bodies contribute to its force law besides their
+// motion: fixed while the list holds.
+struct ContactConst {
+    double Reff, meff;
+    double zmin;      // least gap of the lubrication law
+    double u_crit;    // critical impact speed (Hertz)
+    double kn;        // Hertz: stiffness at or under u_crit; linear: the stiffness
+    double dn;        // normal damping
+};
+
+__device__ __forceinline__ ContactConst contact_const(const PairC &P, double Reff, double meff,
+                                                      double Rmin, double rhod, double kgrav)
+{
+    ContactConst K;
+    K.Reff = Reff;
+    K.meff = meff;
+    K.zmin = P.zeta_min_factor * Rmin;
+    if (P.normal_model == 1) {
+        K.u_crit = 9.0 * P.St_crit * P.rho_f * P.nu_f / rhod;
+        const double kcrit =
+            K.u_crit > 0.0 ? P.K_hz * meff / (sqrt(K.u_crit) * P.Tc52) : 0.0;
+        K.kn = kcrit > kgrav ? kcrit : kgrav;
+        K.dn = P.D_hz * meff / P.T_c;
+    } else {
+        K.u_crit = 0.0;
+        K.kn = meff * P.lin_k / (P.T_c * P.T_c);
+        K.dn = -2.0 * meff * P.le / P.T_c;
+    }
+    return K;
+}
+
+__device__ __forceinline__ ContactConst pair_const(const PairC &P, double mp, double Rp, double mq,
+                                                   double Rq)
+{
+    const double kgp = kn_grav(P, mp, Rp), kgq = kn_grav(P, mq, Rq);
+    return contact_const(P, Rp * Rq / (Rp + Rq), mp * mq / (mp + mq), Rp < Rq ? Rp : Rq,
+                         0.5 * (rho_d(mp, Rp) + rho_d(mq, Rq)), kgp > kgq ? kgp : kgq);
+}
+
+// the wall as a partner of infinite radius and mass
+__device__ __forceinline__ ContactConst wall_const(const PairC &P, double mp, double Rp)
+{
+    return contact_const(P, Rp, mp, Rp, rho_d(mp, Rp), kn_grav(P, mp, Rp));
+}
+
 // ---------------------------------------------------------------------------
 // collision law for one contact (force on p; n points from p to the partner)
 //   lubrication   0 <= zeta < eps_sep: -6 pi rho_f nu_f R_eff^2 psi / zz g_n
@@ -104,9 +149,10 @@ __device__ __forceinline__ double kn_grav(const PairC &P, double m, double R)
 // History hold/hnew: tangential spring (3), impact speed; dt is the time
 // since the state the history belongs to.
 // ---------------------------------------------------------------------------
-__device__ void contact_law(const PairC &P, double zeta, const double *n, const double *g,
-                            double Reff, double meff, double zmin, double rhod, double kgrav,
-                            const double *hold, double dt, double *F, double *Ft, double *hnew)
+__device__ __forceinline__ void contact_law(const PairC &P, double zeta, const double *n,
+                                            const double *g, const ContactConst &K,
+                                            const double *hold, double dt, double *F, double *Ft,
+                                            double *hnew)
 {
     double gn = g[0] * n[0] + g[1] * n[1] + g[2] * n[2];
     double gnv[3], gtv[3];
@@ -121,37 +167,29 @@ __device__ void contact_law(const PairC &P, double zeta, const double *n, const 
     if (zeta >= P.eps_sep)
         return;
     if (zeta >= 0.0) {
-        double zz = zeta > zmin ? zeta : zmin;
+        double zz = zeta > K.zmin ? zeta : K.zmin;
         double psi = 0.5 * erf(6.0 - P.lub_C * zz / P.h) + 0.5;
-        double coef = 6.0 * M_PI * P.rho_f * P.nu_f * Reff * Reff * psi / zz;
+        double coef = 6.0 * M_PI * P.rho_f * P.nu_f * K.Reff * K.Reff * psi / zz;
         for (int a = 0; a < 3; ++a)
             F[a] = -coef * gnv[a];
         return;
     }
     const double u_in = hold[3] > 0.0 ? hold[3] : (gn > 0.0 ? gn : 0.0);
     const double ze = fabs(zeta);
-    double kn, dn, ks, Fn[3];
+    double kn = K.kn, ks, Fn[3];
     if (P.normal_model == 1) {
-        const double u_crit = 9.0 * P.St_crit * P.rho_f * P.nu_f / rhod;
-        if (u_in > u_crit) {
-            kn = P.K_hz * meff / (sqrt(u_in) * P.Tc52);
-        } else {
-            double kcrit = u_crit > 0.0 ? P.K_hz * meff / (sqrt(u_crit) * P.Tc52) : 0.0;
-            kn = kcrit > kgrav ? kcrit : kgrav;
-        }
-        dn = P.D_hz * meff / P.T_c;
+        if (u_in > K.u_crit)
+            kn = P.K_hz * K.meff / (sqrt(u_in) * P.Tc52);
         ks = kn * sqrt(ze);
         for (int a = 0; a < 3; ++a)
-            Fn[a] = -kn * (ze * sqrt(ze)) * n[a] - dn * gnv[a];
+            Fn[a] = -kn * (ze * sqrt(ze)) * n[a] - K.dn * gnv[a];
     } else {
-        kn = meff * P.lin_k / (P.T_c * P.T_c);
-        dn = -2.0 * meff * P.le / P.T_c;
         ks = kn;
         for (int a = 0; a < 3; ++a)
-            Fn[a] = -kn * ze * n[a] - dn * gnv[a];
+            Fn[a] = -kn * ze * n[a] - K.dn * gnv[a];
     }
     double kt = P.kt_ratio * ks;
-    double dtc = 2.0 * sqrt(meff * kt) * (-P.le) / P.sq_damp;
+    double dtc = 2.0 * sqrt(K.meff * kt) * (-P.le) / P.sq_damp;
     double zon = hold[0] * n[0] + hold[1] * n[1] + hold[2] * n[2];
     double zt[3], Fdp[3];
     for (int a = 0; a < 3; ++a) {
@@ -176,81 +214,107 @@ __device__ void contact_law(const PairC &P, double zeta, const double *n, const 
     hnew[3] = u_in;
 }
 
-// Pair (p, q) of the list, p its first particle: force on p, torques on p
-// and q, new history.  g = (u_p - u_q) + R_p,cp w_p x n + R_q,cp w_q x n with
-// the lever arms R_p,cp = (d + R_p - R_q)/2, R_q,cp = (d + R_q - R_p)/2.
-__device__ void pair_contact(const PairC &P, int np, const double *xp, const double *up,
-                             const double *wp, const double *radius, const double *mass, int p,
-                             int q, const double *hold, double dt, double *F, double *Tp,
-                             double *Tq, double *hnew)
+// motion of one particle
+struct BodyState {
+    double x[3], u[3], w[3], R;
+};
+
+// a contact's geometry: gap, normal, relative velocity at the contact point
+// and the lever arms of the two bodies
+struct ContactGeom {
+    double zeta, n[3], g[3], arm_p, arm_q;
+};
+
+// Pair (p, q) of the list, p its first particle: g = (u_p - u_q) +
+// R_p,cp w_p x n + R_q,cp w_q x n with the lever arms R_p,cp =
+// (d + R_p - R_q)/2, R_q,cp = (d + R_q - R_p)/2.
+__device__ __forceinline__ void pair_geometry(const PairC &P, const BodyState &p,
+                                              const BodyState &q, ContactGeom &G)
 {
     double xa[3], xb[3], dvec[3];
-    centre(P, np, xp, p, xa);
-    centre(P, np, xp, q, xb);
-    double d = sqrt(disp2(P, xa, xb, dvec));
-    double Rp = radius[p], Rq = radius[q];
-    double zeta = d - Rp - Rq;
-    double n[3] = {dvec[0] / d, dvec[1] / d, dvec[2] / d};
-    double Rpc = 0.5 * (d + Rp - Rq), Rqc = 0.5 * (d + Rq - Rp);
-    double wpp[3], wqq[3];
     for (int a = 0; a < 3; ++a) {
-        wpp[a] = wp[(size_t)a * np + p];
-        wqq[a] = wp[(size_t)a * np + q];
+        xa[a] = P.periodic[a] ? wrap_pos(p.x[a], P.origin[a], P.L[a]) : p.x[a];
+        xb[a] = P.periodic[a] ? wrap_pos(q.x[a], P.origin[a], P.L[a]) : q.x[a];
     }
-    double wpn[3] = {wpp[1] * n[2] - wpp[2] * n[1], wpp[2] * n[0] - wpp[0] * n[2],
-                     wpp[0] * n[1] - wpp[1] * n[0]};
-    double wqn[3] = {wqq[1] * n[2] - wqq[2] * n[1], wqq[2] * n[0] - wqq[0] * n[2],
-                     wqq[0] * n[1] - wqq[1] * n[0]};
-    double g[3];
+    double d = sqrt(disp2(P, xa, xb, dvec));
+    G.zeta = d - p.R - q.R;
     for (int a = 0; a < 3; ++a)
-        g[a] = (up[(size_t)a * np + p] - up[(size_t)a * np + q]) + Rpc * wpn[a] + Rqc * wqn[a];
-    double mp = mass[p], mq = mass[q];
-    double Reff = Rp * Rq / (Rp + Rq);
-    double meff = mp * mq / (mp + mq);
-    double zmin = P.zeta_min_factor * (Rp < Rq ? Rp : Rq);
-    double rhod = 0.5 * (rho_d(mp, Rp) + rho_d(mq, Rq));
-    double kgp = kn_grav(P, mp, Rp), kgq = kn_grav(P, mq, Rq);
-    double Ft[3];
-    contact_law(P, zeta, n, g, Reff, meff, zmin, rhod, kgp > kgq ? kgp : kgq, hold, dt, F, Ft,
-                hnew);
-    double nxFt[3] = {n[1] * Ft[2] - n[2] * Ft[1], n[2] * Ft[0] - n[0] * Ft[2],
-                      n[0] * Ft[1] - n[1] * Ft[0]};
+        G.n[a] = dvec[a] / d;
+    const double *n = G.n;
+    G.arm_p = 0.5 * (d + p.R - q.R);
+    G.arm_q = 0.5 * (d + q.R - p.R);
+    double wpn[3] = {p.w[1] * n[2] - p.w[2] * n[1], p.w[2] * n[0] - p.w[0] * n[2],
+                     p.w[0] * n[1] - p.w[1] * n[0]};
+    double wqn[3] = {q.w[1] * n[2] - q.w[2] * n[1], q.w[2] * n[0] - q.w[0] * n[2],
+                     q.w[0] * n[1] - q.w[1] * n[0]};
+    for (int a = 0; a < 3; ++a)
+        G.g[a] = (p.u[a] - q.u[a]) + G.arm_p * wpn[a] + G.arm_q * wqn[a];
+}
+
+// Wall entry (p, side = 2 axis + upper): the wall at rest, lever arm = the
+// centre's distance to the wall.
+__device__ __forceinline__ void wall_geometry(const PairC &P, const BodyState &p, int side,
+                                              ContactGeom &G)
+{
+    const int ax = side / 2, upper = side % 2;
+    // every axis's distance, then the entry's: a select between the constants
+    // themselves becomes a load from a per-lane address
+    double d3[3];
+    for (int a = 0; a < 3; ++a)
+        d3[a] = upper == 0 ? p.x[a] - P.origin[a] : (P.origin[a] + P.L[a]) - p.x[a];
+    const double dist = ax == 0 ? d3[0] : ax == 1 ? d3[1] : d3[2];
+    G.zeta = dist - p.R;
+    for (int a = 0; a < 3; ++a)
+        G.n[a] = a == ax ? (upper == 0 ? -1.0 : 1.0) : 0.0;
+    const double *n = G.n;
+    double wpn[3] = {p.w[1] * n[2] - p.w[2] * n[1], p.w[2] * n[0] - p.w[0] * n[2],
+                     p.w[0] * n[1] - p.w[1] * n[0]};
+    for (int a = 0; a < 3; ++a)
+        G.g[a] = p.u[a] + dist * wpn[a];
+    G.arm_p = G.arm_q = dist;
+}
+
+// force and torque on one of a contact's bodies (second: the pair's second
+// particle) and the new history
+__device__ __forceinline__ void contact_force(const PairC &P, const ContactGeom &G,
+                                              const ContactConst &K, bool second,
+                                              const double *hold, double dt, double *f6,
+                                              double *hnew)
+{
+    double F[3], Ft[3];
+    contact_law(P, G.zeta, G.n, G.g, K, hold, dt, F, Ft, hnew);
+    const double *n = G.n;
+    const double nxFt[3] = {n[1] * Ft[2] - n[2] * Ft[1], n[2] * Ft[0] - n[0] * Ft[2],
+                            n[0] * Ft[1] - n[1] * Ft[0]};
+    const double arm = second ? G.arm_q : G.arm_p;
     for (int a = 0; a < 3; ++a) {
-        Tp[a] = Rpc * nxFt[a];
-        Tq[a] = Rqc * nxFt[a];
+        f6[a] = second ? -F[a] : F[a];
+        f6[3 + a] = arm * nxFt[a];
     }
 }
 
-// Wall entry (p, side = 2 axis + upper): the wall as a partner of infinite
-// radius and mass at rest, lever arm = the centre's distance to the wall.
-__device__ void wall_contact(const PairC &P, int np, const double *xp, const double *up,
-                             const double *wp, const double *radius, const double *mass, int p,
-                             int side, const double *hold, double dt, double *F, double *T,
-                             double *hnew)
+// kContactLanes lanes serve one particle, kContactParticles a workgroup of one
+// wave: lane j evaluates the particle's adjacency entries j,
+// j + kContactLanes, ... (a pair in its canonical orientation, so both
+// particles of a pair obtain identical values) and leaves force and torque in
+// part; lane j < 6 then adds component j of the chunk's n entries in adjacency
+// order (increasing partner id, walls after).  One wave to a workgroup, so the
+// exchange needs no barrier and no particle waits for another workgroup's wave.
+constexpr int kContactLanes = 8;
+constexpr int kContactBlock = IBMX_WAVE;
+constexpr int kContactParticles = kContactBlock / kContactLanes;
+
+__device__ __forceinline__ double chunk_sum(const double (*part)[6], int j, int n, double acc)
 {
-    int ax = side / 2, upper = side % 2;
-    double x = xp[(size_t)ax * np + p];
-    double top = P.origin[ax] + P.L[ax];
-    double dist = upper == 0 ? (x - P.origin[ax]) : (top - x);
-    double Rp = radius[p], mp = mass[p];
-    double zeta = dist - Rp;
-    double n[3] = {0.0, 0.0, 0.0};
-    n[ax] = upper == 0 ? -1.0 : 1.0;
-    double wpp[3];
-    for (int a = 0; a < 3; ++a)
-        wpp[a] = wp[(size_t)a * np + p];
-    double wpn[3] = {wpp[1] * n[2] - wpp[2] * n[1], wpp[2] * n[0] - wpp[0] * n[2],
-                     wpp[0] * n[1] - wpp[1] * n[0]};
-    double g[3];
-    for (int a = 0; a < 3; ++a)
-        g[a] = up[(size_t)a * np + p] + dist * wpn[a];
-    double Ft[3];
-    contact_law(P, zeta, n, g, Rp, mp, P.zeta_min_factor * Rp, rho_d(mp, Rp), kn_grav(P, mp, Rp),
-                hold, dt, F, Ft, hnew);
-    double nxFt[3] = {n[1] * Ft[2] - n[2] * Ft[1], n[2] * Ft[0] - n[0] * Ft[2],
-                      n[0] * Ft[1] - n[1] * Ft[0]};
-    for (int a = 0; a < 3; ++a)
-        T[a] = dist * nxFt[a];
+    double v[kContactLanes];
+    const int first = threadIdx.x - j, q = j < 6 ? j : 5;
+#pragma unroll
+    for (int t = 0; t < kContactLanes; ++t)
+        v[t] = part[first + t][q];
+#pragma unroll
+    for (int t = 0; t < kContactLanes; ++t)
+        acc = t < n ? acc + v[t] : acc;
+    return acc;
 }
 
 // ---------------------------------------------------------------------------
@@ -359,195 +423,6 @@ struct Hist {
     double *pair;
     double *wall;
 };
-struct HistC {
-    const double *pair;
-    const double *wall;
-};
-
-// ---------------------------------------------------------------------------
-// one contact evaluation of every particle, optionally followed by a stage
-// of the particle update
-//
-// kContactLanes lanes serve one particle: lane j evaluates the particle's
-// adjacency entries j, j + kContactLanes, ... (the pair in its canonical
-// orientation, so both particles of a pair obtain identical values), the
-// particle's first lane sums the results in adjacency order (increasing
-// partner id, walls after) and applies the update.  With hnew set, each
-// pair's first particle and each wall's particle write the new history.
-// ---------------------------------------------------------------------------
-constexpr int kContactLanes = 8;
-constexpr int kContactBlock = 256;
-
-enum { kStageForces = 0, kStagePredict = 1, kStageCorrect = 2 };
-
-struct Stage {
-    double dts;       // sub-step length
-    double a2;        // 2 alpha_k
-    double alpha;     // alpha_k
-    double gamma;     // gamma_k
-    double zeta;      // zeta_k
-};
-
-struct Body {
-    const double *radius, *mass;
-    const double *Fh, *Th;   // or null
-    const double *sF;        // per-particle factor of F_h, T_h
-};
-
-struct StageIO {
-    const double *xs, *us, *ws;   // state the contacts are evaluated at
-    double *xa, *ua, *wa;         // accepted state (own entries updated by the corrector)
-    double *xt, *ut, *wt;         // predicted state (written by the predictor)
-    double *Fcur;                 // [6][np] force and torque at the accepted state
-    const double *Fprev;          // [6][np] the same one stage earlier
-    double *Fc, *Tc;              // forces mode: outputs (or null)
-};
-
-// the contribution of adjacency entry ea to particle p: F (3), T (3)
-__device__ __forceinline__ void entry_contact(const PairC &P, int np, const ContactLists &C,
-                                              int p, int2 ea, const double *xs, const double *us,
-                                              const double *ws, const double *radius,
-                                              const double *mass, HistC hold, double dt,
-                                              Hist hnew, double *f6)
-{
-    double ho[kHist], hn[kHist], f[3], t1[3], t2[3];
-    const int e = ea.x;
-    if (e >= 0) {
-        const int k = e >> 1;
-        for (int a = 0; a < kHist; ++a)
-            ho[a] = hold.pair[(size_t)a * C.pair_cap + k];
-        const int i = (e & 1) ? ea.y : p, j = (e & 1) ? p : ea.y;
-        pair_contact(P, np, xs, us, ws, radius, mass, i, j, ho, dt, f, t1, t2, hn);
-        if (e & 1) {
-            for (int a = 0; a < 3; ++a) {
-                f6[a] = -f[a];
-                f6[3 + a] = t2[a];
-            }
-        } else {
-            for (int a = 0; a < 3; ++a) {
-                f6[a] = f[a];
-                f6[3 + a] = t1[a];
-            }
-            if (hnew.pair)
-                for (int a = 0; a < kHist; ++a)
-                    hnew.pair[(size_t)a * C.pair_cap + k] = hn[a];
-        }
-    } else {
-        const int k = -e - 1;
-        for (int a = 0; a < kHist; ++a)
-            ho[a] = hold.wall[(size_t)a * C.wall_cap + k];
-        wall_contact(P, np, xs, us, ws, radius, mass, p, ea.y, ho, dt, f, t1, hn);
-        for (int a = 0; a < 3; ++a) {
-            f6[a] = f[a];
-            f6[3 + a] = t1[a];
-        }
-        if (hnew.wall)
-            for (int a = 0; a < kHist; ++a)
-                hnew.wall[(size_t)a * C.wall_cap + k] = hn[a];
-    }
-}
-
-// particle constants: I = 2/5 m R^2, g' = (1 - rho_f / rho_p) g
-__device__ __forceinline__ void body_terms(const PairC &P, const Body &B, int p, double &m,
-                                           double &I, double *gp)
-{
-    m = B.mass[p];
-    const double R = B.radius[p];
-    I = 0.4 * m * R * R;
-    const double rho_p = m / (4.0 / 3.0 * M_PI * R * R * R);
-    for (int a = 0; a < 3; ++a)
-        gp[a] = (1.0 - P.rho_f / rho_p) * P.g[a];
-}
-
-template <int MODE>
-__global__ __launch_bounds__(kContactBlock) void k_contact_stage(PairC P, int np, ContactLists C,
-                                                                const int *off, const int2 *adj,
-                                                                Body B, HistC hold, double dt,
-                                                                Hist hnew, StageIO io, Stage S)
-{
-    __shared__ double part[kContactBlock][6];
-    __shared__ int chunks;
-    const int g = threadIdx.x / kContactLanes, j = threadIdx.x % kContactLanes;
-    const int p = blockIdx.x * (kContactBlock / kContactLanes) + g;
-    int lo = 0, deg = 0;
-    if (p < np) {
-        lo = off[p];
-        deg = off[p + 1] - lo;
-    }
-    if (threadIdx.x == 0)
-        chunks = 0;
-    __syncthreads();
-    if (j == 0 && deg > 0)
-        atomicMax(&chunks, (deg + kContactLanes - 1) / kContactLanes);
-    __syncthreads();
-    const int nch = chunks;
-    double F[3] = {0.0, 0.0, 0.0}, T[3] = {0.0, 0.0, 0.0};
-    for (int c = 0; c < nch; ++c) {
-        const int r = c * kContactLanes + j;
-        if (r < deg) {
-            double f6[6];
-            entry_contact(P, np, C, p, adj[lo + r], io.xs, io.us, io.ws, B.radius, B.mass, hold,
-                          dt, hnew, f6);
-            for (int q = 0; q < 6; ++q)
-                part[threadIdx.x][q] = f6[q];
-        }
-        __syncthreads();
-        if (j == 0) {
-            const int n = min(kContactLanes, deg - c * kContactLanes);
-            for (int t = 0; t < n; ++t)
-                for (int a = 0; a < 3; ++a) {
-                    F[a] = F[a] + part[threadIdx.x + t][a];
-                    T[a] = T[a] + part[threadIdx.x + t][3 + a];
-                }
-        }
-        __syncthreads();
-    }
-    if (j != 0 || p >= np)
-        return;
-    if (MODE == kStageForces) {
-        if (io.Fc)
-            for (int a = 0; a < 3; ++a) {
-                io.Fc[(size_t)a * np + p] = F[a];
-                io.Tc[(size_t)a * np + p] = T[a];
-            }
-        return;
-    }
-    // the particle's own inputs are loaded only now: loading them before the
-    // contacts raises the register count past three waves per SIMD
-    double m, I, gp[3];
-    body_terms(P, B, p, m, I, gp);
-    const double sF = B.sF[p];
-    for (int a = 0; a < 3; ++a) {
-        const size_t i = (size_t)a * np + p;
-        const double Fh = B.Fh ? sF * B.Fh[i] : 0.0, Th = B.Th ? sF * B.Th[i] : 0.0;
-        const double u0 = io.ua[i], w0 = io.wa[i], x0 = io.xa[i];
-        if (MODE == kStagePredict) {
-            // F, T: the accepted state's force, kept for the corrector and
-            // the next stage
-            io.Fcur[i] = F[a];
-            io.Fcur[(size_t)3 * np + i] = T[a];
-            double fs = S.a2 * Fh + S.gamma * F[a];
-            double ts = S.a2 * Th + S.gamma * T[a];
-            if (S.zeta != 0.0) {
-                fs = fs + S.zeta * io.Fprev[i];
-                ts = ts + S.zeta * io.Fprev[(size_t)3 * np + i];
-            }
-            const double u1 = u0 + S.dts / m * fs + S.a2 * S.dts * gp[a];
-            io.ut[i] = u1;
-            io.wt[i] = w0 + S.dts / I * ts;
-            io.xt[i] = x0 + S.alpha * S.dts * (u1 + u0);
-        } else {
-            // F, T: the predicted state's force
-            const double fs = S.a2 * Fh + S.gamma * F[a] + S.zeta * io.Fcur[i];
-            const double ts = S.a2 * Th + S.gamma * T[a] + S.zeta * io.Fcur[(size_t)3 * np + i];
-            const double u1 = u0 + S.dts / m * fs + S.a2 * S.dts * gp[a];
-            const double w1 = w0 + S.dts / I * ts;
-            io.xa[i] = x0 + S.alpha * S.dts * (u1 + u0);
-            io.ua[i] = u1;
-            io.wa[i] = w1;
-        }
-    }
-}
 
 // Method parameters and the host-derived collision constants (everything
 // but the cell grid).
@@ -588,20 +463,6 @@ inline void contact_constants(const ibmx_plan p, PairC *P)
 }
 
 inline int contact_blocks(long long n, int b) { return n > 0 ? (int)((n + b - 1) / b) : 1; }
-
-// One contact evaluation of every particle (and a stage update with MODE
-// kStagePredict / kStageCorrect).
-template <int MODE>
-inline void contact_stage(const PairC &P, int np, const ContactLists &C, const int *off,
-                          const int2 *adj, const Body &B, HistC hold, double dt, Hist hnew,
-                          const StageIO &io, const Stage &S, hipStream_t s)
-{
-    if (np <= 0)
-        return;
-    const int per = kContactBlock / kContactLanes;
-    hipLaunchKernelGGL(k_contact_stage<MODE>, dim3((np + per - 1) / per), dim3(kContactBlock), 0,
-                       s, P, np, C, off, adj, B, hold, dt, hnew, io, S);
-}
 
 // Adjacency of the lists in C into the plan's contact workspace (c_off,
 // c_adj), which holds np + 1 offsets and 2 pair_cap + wall_cap entries.

@@ -98,7 +98,7 @@ struct ibmx_plan_s {
     long long c_adj_cap;
     double *c_hist;       // [c_hist_cap] history buffers
     long long c_hist_cap;
-    double *s_buf;        // [s_cap] sub-step states, stage forces, F_h factors
+    double *s_buf;        // [s_cap] sub-step records, stage forces, entries, constants
     long long s_cap;
 
     // fluid-solve workspace (first ibmx_project / ibmx_fluid_helmholtz call)
@@ -171,7 +171,7 @@ ibmx_status ibmx_contact_reserve(ibmx_plan p, int pair_cap, int wall_cap, int hi
 // whether the contact workspace serves these capacities
 bool ibmx_contact_ready(ibmx_plan p, int pair_cap, int wall_cap, int hist_sets);
 // doubles of sub-stepping state for np particles
-long long ibmx_substep_doubles(int np);
+long long ibmx_substep_doubles(int np, long long nadj);
 // bytes of the adjoint's workspace
 size_t ibmx_backward_bytes(ibmx_plan p);
 // fluid-solve workspace: grid support, presence, allocation

@@ -396,6 +396,83 @@ __global__ void k_hist_align(ContactLists C, int n_in, const int *pairs_in, cons
     }
 }
 
+__device__ __forceinline__ BodyState body_state(int np, const double *xp, const double *up,
+                                                const double *wp, const double *radius, int p)
+{
+    BodyState s;
+    for (int a = 0; a < 3; ++a) {
+        const size_t i = (size_t)a * np + p;
+        s.x[a] = xp[i];
+        s.u[a] = up[i];
+        s.w[a] = wp[i];
+    }
+    s.R = radius[p];
+    return s;
+}
+
+// ---------------------------------------------------------------------------
+// contact forces and torques of every particle (Fc, Tc, or null) and the new
+// history, written by each pair's first particle and each wall's particle
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(kContactBlock) void k_contact_forces(
+    PairC P, int np, ContactLists C, const int *__restrict__ off, const int2 *__restrict__ adj,
+    const double *__restrict__ xp, const double *__restrict__ up, const double *__restrict__ wp,
+    const double *__restrict__ radius, const double *__restrict__ mass, Hist hold, Hist hnew,
+    double *__restrict__ Fc, double *__restrict__ Tc)
+{
+    __shared__ double part[kContactBlock][6];
+    const int j = threadIdx.x % kContactLanes;
+    const int p = blockIdx.x * kContactParticles + threadIdx.x / kContactLanes;
+    int lo = 0, deg = 0;
+    if (p < np) {
+        lo = off[p];
+        deg = off[p + 1] - lo;
+    }
+    double acc = 0.0;
+    for (int c = 0; __any(c * kContactLanes < deg); ++c) {
+        const int r = c * kContactLanes + j;
+        if (r < deg) {
+            const int2 e = adj[lo + r];
+            double ho[kHist], hn[kHist];
+            ContactGeom G;
+            ContactConst K;
+            const bool pair = e.x >= 0, second = pair && (e.x & 1);
+            const int k = pair ? e.x >> 1 : -e.x - 1;
+            if (pair) {
+                for (int a = 0; a < kHist; ++a)
+                    ho[a] = hold.pair[(size_t)a * C.pair_cap + k];
+                const int i1 = second ? e.y : p, i2 = second ? p : e.y;
+                const BodyState s1 = body_state(np, xp, up, wp, radius, i1);
+                const BodyState s2 = body_state(np, xp, up, wp, radius, i2);
+                pair_geometry(P, s1, s2, G);
+                K = pair_const(P, mass[i1], s1.R, mass[i2], s2.R);
+            } else {
+                for (int a = 0; a < kHist; ++a)
+                    ho[a] = hold.wall[(size_t)a * C.wall_cap + k];
+                const BodyState s1 = body_state(np, xp, up, wp, radius, p);
+                wall_geometry(P, s1, e.y, G);
+                K = wall_const(P, mass[p], s1.R);
+            }
+            contact_force(P, G, K, second, ho, P.dt, part[threadIdx.x], hn);
+            if (pair && !second && hnew.pair)
+                for (int a = 0; a < kHist; ++a)
+                    hnew.pair[(size_t)a * C.pair_cap + k] = hn[a];
+            if (!pair && hnew.wall)
+                for (int a = 0; a < kHist; ++a)
+                    hnew.wall[(size_t)a * C.wall_cap + k] = hn[a];
+        }
+        __syncthreads();
+        acc = chunk_sum(part, j, deg - c * kContactLanes, acc);
+        __syncthreads();
+    }
+    if (p >= np || j >= 6 || !Fc)
+        return;
+    if (j < 3)
+        Fc[(size_t)j * np + p] = acc;
+    else
+        Tc[(size_t)(j - 3) * np + p] = acc;
+}
+
 // ---------------------------------------------------------------------------
 // marker-disable mask
 // ---------------------------------------------------------------------------
@@ -618,16 +695,11 @@ extern "C" ibmx_status ibmx_pairs(ibmx_plan p, const double *xp, const double *r
                            nwall_in, walls_in, whist_in, hold);
     }
     contact_adjacency(p, C, s);
-    StageIO io{};
-    io.xs = xp;
-    io.us = up;
-    io.ws = wp;
-    io.Fc = Fc;
-    io.Tc = Tc;
-    contact_stage<kStageForces>(P, np, C, p->c_off, (const int2 *)p->c_adj,
-                                Body{radius, mass, nullptr, nullptr, nullptr},
-                                HistC{hold.pair, hold.wall}, P.dt, Hist{hist_out, whist_out}, io,
-                                Stage{}, s);
+    if (np > 0)
+        hipLaunchKernelGGL(k_contact_forces, dim3(blocks(np, kContactParticles)),
+                           dim3(kContactBlock), 0, s, P, np, C, (const int *)p->c_off,
+                           (const int2 *)p->c_adj, xp, up, wp, radius, mass, hold,
+                           Hist{hist_out, whist_out}, Fc, Tc);
     // mask
     if (marker_active && nm > 0) {
         if (prm.disable_mode == 0)

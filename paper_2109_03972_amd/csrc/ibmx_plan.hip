@@ -504,7 +504,12 @@ ibmx_status ibmx_plan_actm(ibmx_plan p)
     return IBMX_OK;
 }
 
-long long ibmx_substep_doubles(int np) { return 22LL * (np > 0 ? np : 1); }
+// per particle two records of 16, two stage forces of 8 and 8 adjacency entries
+// of one double's size; 6 constants per adjacency entry
+long long ibmx_substep_doubles(int np, long long nadj)
+{
+    return 56LL * (np > 0 ? np : 1) + 6 * nadj;
+}
 
 bool ibmx_contact_ready(ibmx_plan p, int pair_cap, int wall_cap, int hist_sets)
 {
@@ -539,7 +544,7 @@ extern "C" ibmx_status ibmx_plan_reserve(ibmx_plan p, int32_t pair_cap, int32_t 
     // contact adjacency and two history sets (the sub-steps alternate them)
     if (ibmx_contact_reserve(p, pair_cap, wall_cap, 2) != IBMX_OK)
         return IBMX_ENOMEM;
-    const long long need = ibmx_substep_doubles(p->np);
+    const long long need = ibmx_substep_doubles(p->np, p->c_adj_cap);
     if (!p->s_buf || p->s_cap < need) {
         if (p->s_buf)
             (void)hipFree(p->s_buf);

@@ -132,6 +132,35 @@ def test_wall_contacts(model):
     _compare(got, ref)
 
 
+@pytest.mark.parametrize("around", [8, 9, 19])
+@pytest.mark.parametrize("model", [0, 1])
+def test_contacts_above_one_round(model, around):
+    """A sphere with 8, 9 and 19 partners (its contacts are evaluated eight at
+    a time) next to a wall, in particle counts that leave the last workgroup
+    partly empty; same tolerance as the other sub-step cases."""
+    rng = np.random.default_rng(311 + around)
+    k = np.arange(around) + 0.5
+    polar, turn = np.arccos(1.0 - 2.0 * k / around), np.pi * (1.0 + 5.0 ** 0.5) * k
+    unit = np.array([np.cos(turn) * np.sin(polar), np.sin(turn) * np.sin(polar), np.cos(polar)])
+    R = np.concatenate([[11.0], np.full(around, 3.0)])
+    x = np.empty((3, around + 1))
+    x[:, 0] = (32.0, 30.0, 17.2)
+    x[:, 1:] = x[:, :1] + unit * (14.0 + rng.uniform(-0.2, 0.4, around))
+    prm = synth.default_params()
+    prm.update(gap_cut=2.0, normal_model=model, gravity=(0.0, 0.0, -2e-3), disable_mode=0)
+    c = synth.Case(name="crowd", n=(64, 60, 48), h=1.0, origin=(0.0, 0.0, 0.0),
+                   periodic=(1, 1, 0), xp=np.ascontiguousarray(x),
+                   up=rng.normal(0, 0.03, x.shape), wp=rng.normal(0, 0.01, x.shape), radius=R,
+                   mass=2.5 * 4.0 / 3.0 * np.pi * R ** 3,
+                   moff=np.zeros(R.size + 1, dtype=np.int32), body=np.zeros((3, 0)),
+                   dV=np.ones(R.size), u0=None, params=prm)
+    got, ref, ref_l = _run_both(c, 1.0, 5, seed=7)
+    got["x0"] = x
+    assert np.bincount(ref_l["pairs"].ravel())[0] == around
+    assert np.any(ref_l["gap"] < 0) and np.any(ref_l["gap"] > 0)
+    _compare(got, ref)
+
+
 def test_fp32_plan():
     """The contact pass is FP64 whatever the plan's grid precision."""
     c = _wall_layer(308)
