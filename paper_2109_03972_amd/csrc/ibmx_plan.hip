@@ -218,10 +218,16 @@ ibmx_status check_params(const ibmx_grid *g, const ibmx_params *prm)
         free_plan(p);
         return st;
     }
-    // default tiles: 16 x 16 x 8 nodes
+    // default tiles: 16 x 16 x 8 nodes; FP64 with the four-point delta 16 x 8 x 8:
+    // the interpolation's region of the larger tile, 19 x 19 x 11 nodes, takes
+    // 95 KB of LDS and leaves one workgroup per CU, that of 19 x 11 x 11 nodes
+    // 55 KB and two.  FP64, four-point: 128^3 with 200 spheres 396 -> 370 us,
+    // 256 x 256 x 512 with 2000 7.57 -> 7.32 ms, 71 x 69 x 254 with 17 249 ->
+    // 189 us.  The three-point one (78 KB, two workgroups) loses by the larger
+    // halo: 247 -> 262 us and 4.29 -> 5.09 ms on the first two.
     st = ibmx_plan_scan_reserve(p, np);
     if (st == IBMX_OK)
-        st = ibmx_plan_alloc_tiles(p, 16, 16, 8);
+        st = ibmx_plan_alloc_tiles(p, 16, p->prec == IBMX_F64 && p->prm.kernel == 4 ? 8 : 16, 8);
     if (st != IBMX_OK) {
         free_plan(p);
         return st;

@@ -226,6 +226,25 @@ def test_tile_shapes_parity_four_point(oracle_lib, tile):
             assert e <= tol, f"{precision} tile {tile} {k}: {e:.3e}"
 
 
+@pytest.mark.parametrize("kernel,precision,tile", [
+    (3, "f32", (16, 16, 8)), (3, "f64", (16, 16, 8)), (4, "f32", (16, 16, 8)),
+    (4, "f64", (16, 8, 8))])
+def test_default_tiles_parity(oracle_lib, kernel, precision, tile):
+    """The shape a plan starts with, per delta and precision, against the
+    oracle."""
+    dev = require_gpu()
+    case = synth.small_case(77, n=(48, 40, 48), periodic=(1, 1, 0), n_iter=2, touch=0.4)
+    case.params.update(kernel=kernel, eps_sep=2.0, lub_C=4.0, gap_cut=4.0)
+    m_np, mk = _mask(case, dev)
+    ref = oracle_lib.forcing(case, mask=m_np, kernel=kernel)
+    plan, D = _setup(case, precision)
+    assert plan.stats()["tile"] == tile
+    got = _run(plan, D, D["u"].clone(), mk, False)
+    for k in ("u", "f_tot", "S", "T"):
+        e = rel_err(got[k], ref[k])
+        assert e <= (1e-12 if precision == "f64" else 1e-4), f"{k}: {e:.3e}"
+
+
 def test_set_tiles_rejects_bad_shapes():
     from paper_2109_03972_amd import ibmx
     require_gpu()
