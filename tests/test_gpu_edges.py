@@ -195,3 +195,30 @@ def test_dense_markers_spread_exactly(precision, kernel):
         e = rel_err(got[k], ref[k])
         print(f"  {k}: {e:.2e}", flush=True)
         assert e <= t, (k, e)
+
+
+@pytest.mark.parametrize("tile", [(4, 4, 4), (16, 16, 8)])
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+def test_markers_all_over_the_tiles(precision, tile):
+    """Markers strewn over the box: 256 consecutive ones reach some 600 tiles
+    of 4^3 nodes, more than a workgroup of the binning counts in its table
+    (256), and 45 tiles of 16 x 16 x 8, which it does; tolerances as
+    above."""
+    base = synth.small_case(312, n=(48, 44, 40), periodic=(1, 1, 0), diameters=(8.0,),
+                            n_iter=2, touch=0.0, disable_mode=0)
+    rng = np.random.default_rng(312)
+    nl = 1000                                        # the last workgroup is partly empty
+    X = np.array([rng.uniform(3.0, m - 3.0, nl) for m in base.n])
+    case = synth.Case(name="strewn", n=base.n, h=base.h, origin=base.origin,
+                      periodic=base.periodic, xp=base.xp, up=base.up, wp=base.wp,
+                      radius=base.radius, mass=base.mass,
+                      moff=np.array([0, nl], dtype=np.int32),
+                      body=np.ascontiguousarray(X - base.xp), dV=np.array([1.0]), u0=base.u0,
+                      params=dict(base.params))
+    ref = oracle.forcing(case, want_U=True)
+    mask = np.ones(nl, dtype=np.uint8)
+    got, plan, _ = _run(case, precision, mask, tile)
+    assert got["status"] == 0
+    for k, t in TOL[precision].items():
+        e = rel_err(got[k], ref[k])
+        assert e <= t, f"{k}: {e:.2e}"
