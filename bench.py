@@ -118,12 +118,15 @@ def fluid_bytes(kind: str, s: int, nodes: int, walls_z: bool = True) -> float:
     row, about 8 B per node, and on an FP64 real grid, 8 B per node).
 
     spectrum (one solve between the x passes): the y pass forward and back
-           (read and write 8 each: 16 + 16), and across walls the elimination
-           (read and write the spectrum twice: 32; the eliminated coefficient
-           is stored only until it becomes constant along z, not counted) or
-           along a periodic z two more passes and the division (48).
+           (read and write 8 each: 16 + 16), and across walls an elimination
+           (read and write the spectrum twice: 32) or along a periodic z two
+           more passes and the division (48).  This is the count of the
+           textbook forms, kept so that rates stay comparable; where the
+           solve along z runs as one pass it moves 16, so a rate by these
+           bytes can lie above what the memory moves.
     predictor: reads u, N (3s each) and P (s); writes u~, N and nu L u (3s each).
-    project: face values and divergence (reads 3s, writes 3s + 8), the
+    project: face values and divergence (reads 3s, writes 3s + 8; the
+           library writes u_f there only on the rims of its columns), the
            forward x pass from the real grid (read 8, write 8), the spectrum,
            the inverse x pass into the real grid (16), the correction (reads
            the solution, u, u_f, P; writes u, u_f, P: 8 + 14s; phi is not
@@ -512,7 +515,8 @@ def main():
                          note="the collocated solver's other steps of one Runge-Kutta stage on "
                               "the workload's grid (FP32 fields): ibmx_fluid_predictor, "
                               "ibmx_fluid_helmholtz and ibmx_project (FP64 FFT/tridiagonal "
-                              "solves); not part of the step"),
+                              "solves); bytes of the textbook solves, of which the one-pass "
+                              "solve along z moves 16 per node less; not part of the step"),
         substeps=dict(ms=r32["extras"]["substeps_ms"], n_sub=r32["extras"]["substeps_n_sub"],
                       particles=case.np_, cpu_oracle_ms=cpu_sub_ms,
                       note="ibmx_particle_substeps of one time step (Hertz/ACTM contacts, "

@@ -236,7 +236,7 @@ __device__ __forceinline__ HaloSet halo_tiles(const GridC &g, const TileC &tc, c
 // workgroup goes to memory.  Looking the lanes' tiles up costs a broadcast read
 // and an LDS atomic; collecting the equal tiles of each wave by ballots took a
 // scalar loop over some 20 groups and four times the atomics.  10.6M markers on
-// 512^3, FP32: count 254 -> 158 us (0.35 GB), scatter 388 -> 248 us (0.8 GB);
+// 512^3, FP32: count 254 -> 158 us (0.42 GB), scatter 388 -> 248 us (0.95 GB);
 // 1.34M on 256 x 256 x 512: 72 -> 26 and 65 -> 33 us.
 constexpr int BIN_BLOCK = 256, BIN_SLOTS = BIN_BLOCK;   // one slot per thread
 
