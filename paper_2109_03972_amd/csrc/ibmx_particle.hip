@@ -132,15 +132,19 @@ __global__ __launch_bounds__(WP == 1 ? 256 : 64 * WP) void k_particle_integrals(
                 r[a] = c0[a] + 0.5 * h;
             }
             const double alpha = cell_alpha(c0, h, R);
-            const double w[3] = {alpha * uc[0], alpha * uc[1], alpha * uc[2]};
-            s[0] += w[0];
-            s[1] += w[1];
-            s[2] += w[2];
-            s[3] += r[1] * w[2] - r[2] * w[1];
-            s[4] += r[2] * w[0] - r[0] * w[2];
-            s[5] += r[0] * w[1] - r[1] * w[0];
-            if (alpha_out && alpha > 0.0)
-                atomicAdd(&alpha_out[gi], (T)alpha);
+            // a listed cell may still have all its corners outside: whatever the
+            // field holds there (0 * inf) stays out
+            if (alpha != 0.0) {
+                const double w[3] = {alpha * uc[0], alpha * uc[1], alpha * uc[2]};
+                s[0] += w[0];
+                s[1] += w[1];
+                s[2] += w[2];
+                s[3] += r[1] * w[2] - r[2] * w[1];
+                s[4] += r[2] * w[0] - r[0] * w[2];
+                s[5] += r[0] * w[1] - r[1] * w[0];
+                if (alpha_out)
+                    atomicAdd(&alpha_out[gi], (T)alpha);
+            }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();

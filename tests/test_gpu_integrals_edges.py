@@ -1,0 +1,49 @@
+"""Particle integrals at the edges of their inputs: field values that must not
+count."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2109_03972_amd import ibmx, synth
+from tests._util import rel_err, require_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def _spheres(n, x, R, periodic=(1, 1, 0), seed=5):
+    case = synth.small_case(seed, n=n, periodic=periodic, diameters=(6.0,), disable_mode=0)
+    k = len(R)
+    case.xp, case.radius, case.mass = np.ascontiguousarray(x), np.asarray(R), np.ones(k)
+    case.up, case.wp = np.zeros((3, k)), np.zeros((3, k))
+    case.moff, case.body, case.dV = np.zeros(k + 1, np.int32), np.zeros((3, 0)), np.ones(k)
+    return case
+
+
+def _integrals(case, u, precision="f64"):
+    import torch
+    dev = require_gpu()
+    T = torch.float64 if precision == "f64" else torch.float32
+    plan = ibmx.Plan.from_case(case, precision)
+    x, R = (torch.as_tensor(a, device=dev).contiguous() for a in (case.xp, case.radius))
+    Iu, Ir = plan.particle_integrals(torch.as_tensor(u, device=dev).to(T).contiguous(), x, R)
+    plan.check("integrals")
+    plan.close()
+    return Iu.cpu().numpy(), Ir.cpu().numpy()
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+@pytest.mark.parametrize("count", [3, 600, 4200])
+def test_values_outside_the_particles_do_not_count(count, bad):
+    """A NaN or an infinity in every cell of volume fraction 0: the sums are
+    those of a field with 0 there, bit for bit (such a cell is left out)."""
+    n = (72, 64, 80)
+    rng = np.random.default_rng(count)
+    x = rng.random((3, count)) * np.array(n)[:, None]
+    case = _spheres(n, x, rng.uniform(0.7, 2.5 if count > 100 else 9.0, count))
+    alpha = oracle.particle_integrals(case, u=case.u0, want_alpha=True)["alpha"]
+    out = alpha == 0.0
+    assert 0.05 < out.mean() < 1.0
+    want = _integrals(case, np.where(out, 0.0, case.u0))
+    got = _integrals(case, np.where(out, bad, case.u0))
+    for a, b in zip(got, want):
+        np.testing.assert_array_equal(a, b)
