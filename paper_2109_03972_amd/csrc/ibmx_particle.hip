@@ -88,11 +88,14 @@ __global__ __launch_bounds__(WP == 1 ? 256 : 64 * WP) void k_particle_integrals(
             x[a] = x[a] - floor((x[a] - g.origin[a]) / L) * L;
         }
         // cells beyond a wall do not count; a particle over a whole periodic
-        // axis (which is not allowed) stays within one period
+        // axis (which is not allowed) stays within one period; one whose centre
+        // or radius is not finite has no cells (fmax and fmin drop a NaN)
         const double c0 = floor((x[a] - R - g.origin[a]) / h);
         const double c1 = floor((x[a] + R - g.origin[a]) / h);
         const double first = fmax(c0, g.periodic[a] ? -g.n[a] : 0.0);
-        const double end = fmin(c1 + 1.0, g.periodic[a] ? first + g.n[a] : g.n[a]);
+        const double end = isfinite(c1 - c0)
+                               ? fmin(c1 + 1.0, g.periodic[a] ? first + g.n[a] : g.n[a])
+                               : first;
         lo[a] = __builtin_amdgcn_readfirstlane((int)first);
         ext[a] = __builtin_amdgcn_readfirstlane(end > first ? (int)(end - first) : 0);
         wraps[a] = lo[a] < 0 || lo[a] + ext[a] > g.n[a];

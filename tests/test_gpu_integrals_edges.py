@@ -1,5 +1,5 @@
 """Particle integrals at the edges of their inputs: field values that must not
-count."""
+count and particles that are nowhere."""
 import numpy as np
 import pytest
 
@@ -47,3 +47,51 @@ def test_values_outside_the_particles_do_not_count(count, bad):
     got = _integrals(case, np.where(out, bad, case.u0))
     for a, b in zip(got, want):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("what", ["centre", "radius"])
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+@pytest.mark.parametrize("count", [4, 600, 4200])
+def test_particles_that_are_not_finite(count, bad, what):
+    """A particle whose centre or radius is not finite has no cells: its sums
+    are 0, the others' as without it, and a call in which every particle is
+    lost takes no longer than one with small spheres (a walk of this grid by
+    every one took 290 times as long)."""
+    import torch
+    dev = require_gpu()
+    n = (256, 256, 256)
+    rng = np.random.default_rng(count)
+    x, R = rng.random((3, count)) * 256.0, rng.uniform(0.7, 2.5, count)
+    case = _spheres(n, x, R)
+    u = torch.rand((3, 256, 256, 256), dtype=torch.float32, device=dev)
+    plan = ibmx.Plan.from_case(case, "f32")
+
+    def call(x, R, reps=0):
+        X, Q = (torch.as_tensor(a, device=dev).contiguous() for a in (x, R))
+        out = plan.particle_integrals(u, X, Q)
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for _ in range(reps):
+            plan.particle_integrals(u, X, Q)
+        b.record()
+        torch.cuda.synchronize()
+        return [v.cpu().numpy() for v in out], a.elapsed_time(b)
+
+    def lose(which):
+        xb, Rb = x.copy(), R.copy()
+        if what == "radius":
+            Rb[which] = bad
+        else:
+            xb[rng.integers(0, 3, len(which)), which] = bad
+        return xb, Rb
+
+    want, t0 = call(x, R, 10)
+    lost = np.array([1, count - 1])
+    got, _ = call(*lose(lost))
+    for a, b in zip(got, want):
+        assert np.all(a[:, lost] == 0.0)
+        np.testing.assert_array_equal(np.delete(a, lost, 1), np.delete(b, lost, 1))
+    got, t1 = call(*lose(np.arange(count)), 10)
+    assert all(np.all(a == 0.0) for a in got)
+    assert t1 <= 4.0 * t0, (t1, t0)
+    plan.close()
