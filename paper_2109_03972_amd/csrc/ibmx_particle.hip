@@ -67,7 +67,8 @@ __global__ __launch_bounds__(WP == 1 ? 256 : 64 * WP) void k_particle_integrals(
     T *__restrict__ alpha_out)
 {
     constexpr int NW = WP == 1 ? 4 : WP;             // waves per workgroup
-    __shared__ int2 s_list[NW][2 * IBMX_WAVE];
+    // box indices of the listed cells (an axis may be longer than 16 bits)
+    __shared__ int s_list[NW][3][2 * IBMX_WAVE];
     __shared__ double part[6][NW];
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / IBMX_WAVE);
     const int lane = threadIdx.x & (IBMX_WAVE - 1);
@@ -75,7 +76,7 @@ __global__ __launch_bounds__(WP == 1 ? 256 : 64 * WP) void k_particle_integrals(
     const int pw = WP == 1 ? 0 : wv;                 // wave of the particle
     if (WP == 1 && p >= np)
         return;
-    int2 *list = s_list[wv];
+    int (*list)[2 * IBMX_WAVE] = s_list[wv];
     const double h = g.h, h3 = h * h * h, half_diag = 0.5 * sqrt(3.0) * h;
     const double R = radius[p];
     double x[3];
@@ -123,8 +124,7 @@ __global__ __launch_bounds__(WP == 1 ? 256 : 64 * WP) void k_particle_integrals(
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
         if (lane < n) {
-            const int2 e = list[first + lane];
-            const int i[3] = {e.x & 0xffff, (int)((unsigned)e.x >> 16), e.y};
+            const int i[3] = {list[0][first + lane], list[1][first + lane], list[2][first + lane]};
             const unsigned gi =
                 (node(2, i[2]) * (unsigned)g.n[1] + node(1, i[1])) * (unsigned)g.n[0] + node(0, i[0]);
             // the cell's velocity is in flight during the square roots
@@ -186,9 +186,12 @@ __global__ __launch_bounds__(WP == 1 ? 256 : 64 * WP) void k_particle_integrals(
                     atomicAdd(&alpha_out[gi], T(1));
             }
             const unsigned long long mk = __ballot(edge);
-            if (edge)
-                list[listed + __popcll(mk & ((1ull << lane) - 1ull))] =
-                    make_int2(ix | (iy << 16), iz);
+            if (edge) {
+                const int at = listed + __popcll(mk & ((1ull << lane) - 1ull));
+                list[0][at] = ix;
+                list[1][at] = iy;
+                list[2][at] = iz;
+            }
             listed += __popcll(mk);
             if (listed >= IBMX_WAVE) {
                 listed -= IBMX_WAVE;

@@ -1,5 +1,5 @@
 """Particle integrals at the edges of their inputs: field values that must not
-count and particles that are nowhere."""
+count, particles that are nowhere, boxes longer than 16 bits."""
 import numpy as np
 import pytest
 
@@ -95,3 +95,37 @@ def test_particles_that_are_not_finite(count, bad, what):
     assert all(np.all(a == 0.0) for a in got)
     assert t1 <= 4.0 * t0, (t1, t0)
     plan.close()
+
+
+def _plain_integrals(n, x, R, u):
+    """The level-set sums over every cell of a walled box, h = 1."""
+    i = [np.arange(m) - c for m, c in zip(n, x)]
+    num = den = 0.0
+    for m in range(8):
+        d2 = ((i[2] + (m >> 2)) ** 2)[:, None, None] + \
+            ((i[1] + (m >> 1 & 1)) ** 2)[None, :, None] + ((i[0] + (m & 1)) ** 2)[None, None, :]
+        phi = np.sqrt(d2) - R
+        num, den = num + np.maximum(-phi, 0.0), den + np.abs(phi)
+    w = num / den * u
+    r = [(i[2 - a] + 0.5).reshape([-1 if b == a else 1 for b in range(3)]) for a in (2, 1, 0)]
+    Ir = [(r[1] * w[2] - r[2] * w[1]).sum(), (r[2] * w[0] - r[0] * w[2]).sum(),
+          (r[0] * w[1] - r[1] * w[0]).sum()]
+    return w.sum((1, 2, 3)), np.array(Ir)
+
+
+@pytest.mark.parametrize("n", [(80000, 5, 4), (5, 80000, 4), (4, 5, 80000)])
+def test_boxes_longer_than_16_bits(n):
+    """A sphere whose box is 78001 cells long, cut by the lower wall; sums of
+    1.6M values of one sign to FP64 rounding (1e-12)."""
+    rng = np.random.default_rng(1)
+    a = int(np.argmax(n))
+    x = 0.5 * np.array(n) + 0.13
+    x[a] = 38000.3
+    u = 1.0 + rng.random((3, n[2], n[1], n[0]))
+    case = synth.Case(name="long", n=n, h=1.0, origin=(0.0, 0.0, 0.0), periodic=(0, 0, 0),
+                      xp=x[:, None].copy(), up=np.zeros((3, 1)), wp=np.zeros((3, 1)),
+                      radius=np.array([40000.0]), mass=np.ones(1),
+                      moff=np.zeros(2, np.int32), body=np.zeros((3, 0)), dV=np.ones(1), u0=u,
+                      params=dict(synth.default_params(), disable_mode=0))
+    for got, want in zip(_integrals(case, u), _plain_integrals(n, x, 40000.0, u)):
+        assert rel_err(got[:, 0], want) <= 1e-12
