@@ -46,38 +46,24 @@ __device__ __forceinline__ double cell_alpha(const double *c0, double h, double 
     return den > 0.0 ? num / den : 0.0;
 }
 
-// The integrals of one particle by WP waves (four particles per workgroup
-// when WP = 1).  A wave takes whole x rows of the particle's bounding box, as
-// many at a time as fit its lanes.  Cells whose centre lies deeper than half a
-// cell diagonal inside (outside) the surface have every corner inside
-// (outside) and take alpha = 1 (0), which is what the corner formula gives for
-// them; the test compares squared distances.  The cells in between (a third of
-// the box) need eight corner distances: they are collected in the wave's LDS
-// list and taken 64 at a time, so that no lane idles through the square roots
-// of another's cell.  FP64 sums: per lane in a fixed order, per wave by a
-// fixed shuffle tree, over the waves in wave order.
-// Bound by FP64 instructions: the 20,000 spheres of a 512^3 bed, FP32 field,
-// 298 us against 641 with a thread per cell of the box (divisions for the
-// cell's indices, and every wave that met the surface ran the corners for
-// all); four waves a particle there take 349 (part-filled lists).
-template <typename T, int WP, bool O32>
-__global__ __launch_bounds__(WP == 1 ? 256 : 64 * WP) void k_particle_integrals(
-    GridC g, int np, const double *__restrict__ xp, const double *__restrict__ radius,
-    const T *__restrict__ u, double *__restrict__ Iu, double *__restrict__ Ir,
-    T *__restrict__ alpha_out)
+// Wave pw of nw's share of one particle's sums, in every lane: s[0..2] of alpha
+// u, s[3..5] of alpha r x u.  A wave takes whole x rows of the particle's
+// bounding box, as many at a time as fit its lanes.  Cells whose centre lies
+// deeper than half a cell diagonal inside (outside) the surface have every
+// corner inside (outside) and take alpha = 1 (0), which is what the corner
+// formula gives for them; the test compares squared distances.  The cells in
+// between (a third of the box) need eight corner distances: they are collected
+// in the wave's LDS list (their box indices) and taken 64 at a time, so that no
+// lane idles through the square roots of another's cell.
+template <typename T, bool O32>
+__device__ __forceinline__ void sphere_sums(const GridC &g, int np, int p, int pw, int nw,
+                                            const double *__restrict__ xp,
+                                            const double *__restrict__ radius,
+                                            const T *__restrict__ u, T *__restrict__ alpha_out,
+                                            int (*list)[2 * IBMX_WAVE], double *s)
 {
-    constexpr int NW = WP == 1 ? 4 : WP;             // waves per workgroup
-    // box indices of the listed cells (an axis may be longer than 16 bits)
-    __shared__ int s_list[NW][3][2 * IBMX_WAVE];
-    __shared__ double part[6][NW];
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / IBMX_WAVE);
     const int lane = threadIdx.x & (IBMX_WAVE - 1);
-    const int p = WP == 1 ? blockIdx.x * NW + wv : blockIdx.x;
-    const int pw = WP == 1 ? 0 : wv;                 // wave of the particle
-    if (WP == 1 && p >= np)
-        return;
-    int (*list)[2 * IBMX_WAVE] = s_list[wv];
-    const double h = g.h, h3 = h * h * h, half_diag = 0.5 * sqrt(3.0) * h;
+    const double h = g.h, half_diag = 0.5 * sqrt(3.0) * h;
     const double R = radius[p];
     double x[3];
     int lo[3], ext[3];
@@ -104,7 +90,8 @@ __global__ __launch_bounds__(WP == 1 ? 256 : 64 * WP) void k_particle_integrals(
     const double r_in = R - half_diag, r_out = R + half_diag;
     const double r_in2 = r_in > 0.0 ? r_in * r_in : -1.0, r_out2 = r_out * r_out;
     const T *const ub[3] = {u, u + g.nodes, u + 2 * g.nodes};
-    double s[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int k = 0; k < 6; ++k)
+        s[k] = 0.0;
     // lowest corner of cell i along axis a, relative to the centre, and its node
     auto corner = [&](int a, int i) { return g.origin[a] + (lo[a] + i) * h - x[a]; };
     auto node = [&](int a, int i) {
@@ -156,7 +143,7 @@ __global__ __launch_bounds__(WP == 1 ? 256 : 64 * WP) void k_particle_integrals(
     // rows per step
     const int rpi = ext[0] > 0 && ext[0] < IBMX_WAVE ? IBMX_WAVE / ext[0] : 1;
     const int sub = rpi > 1 ? lane / ext[0] : 0, lx = rpi > 1 ? lane - sub * ext[0] : lane;
-    const int rows = ext[1] * ext[2], step = WP * rpi;
+    const int rows = ext[1] * ext[2], step = nw * rpi;
     for (int x0 = 0; x0 < (rows > 0 ? ext[0] : 0); x0 += IBMX_WAVE) {
         const int ix = x0 + lx;
         const bool inx = (sub < rpi) & (ix < ext[0]);
@@ -216,7 +203,49 @@ __global__ __launch_bounds__(WP == 1 ? 256 : 64 * WP) void k_particle_integrals(
 #pragma unroll
     for (int k = 0; k < 6; ++k)
         s[k] = wave_sum(s[k]);
-    if (WP > 1) {
+}
+
+// The integrals of every particle: WP waves each, or (WP = 1) a wave each, four
+// to a workgroup; spheres wider than kShareWidth cells then get a workgroup of
+// their own, from a second range of workgroups, one per particle, of which the
+// others return at once (5000 spheres with one of 100 cells: 2.3 ms, with one
+// wave for it 8.5, with 256 threads for every particle 3.9; looking through the
+// four spheres inside one workgroup cost the bed below another 10 to 20 us in
+// registers).  FP64 sums: per lane in a fixed order, per wave by a fixed shuffle
+// tree, over the waves in wave order.
+// Bound by FP64 instructions: the 20,000 spheres of a 512^3 bed, FP32 field,
+// 311 us against 641 with a thread per cell of the box (divisions for the
+// cell's indices, and every wave that met the surface ran the corners for
+// all); four waves a particle there take 349 (part-filled lists).
+constexpr double kShareWidth = 40.0;
+template <typename T, int WP, bool O32>
+__global__ __launch_bounds__(WP == 1 ? 256 : 64 * WP) void k_particle_integrals(
+    GridC g, int np, const double *__restrict__ xp, const double *__restrict__ radius,
+    const T *__restrict__ u, double *__restrict__ Iu, double *__restrict__ Ir,
+    T *__restrict__ alpha_out)
+{
+    constexpr int NW = WP == 1 ? 4 : WP;             // waves per workgroup
+    __shared__ int s_list[NW][3][2 * IBMX_WAVE];
+    __shared__ double part[6][NW];
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / IBMX_WAVE);
+    const int lane = threadIdx.x & (IBMX_WAVE - 1);
+    const double h3 = g.h * g.h * g.h;
+    auto write = [&](int p, const double *s) {
+        for (int k = 0; k < 3; ++k) {
+            Iu[(size_t)k * np + p] = h3 * s[k];
+            Ir[(size_t)k * np + p] = h3 * s[3 + k];
+        }
+    };
+    // WP = 1: a workgroup per four spheres, then one per sphere for the wide ones
+    const int nb = WP == 1 ? (np + NW - 1) / NW : 0;
+    const bool shared = (int)blockIdx.x >= nb;
+    const int p = __builtin_amdgcn_readfirstlane(shared ? blockIdx.x - nb : blockIdx.x * NW + wv);
+    if (WP == 1 && (p >= np || (2.0 * radius[p] > kShareWidth * g.h) != shared))
+        return;
+    double s[6];
+    sphere_sums<T, O32>(g, np, p, shared ? wv : 0, shared ? NW : 1, xp, radius, u, alpha_out,
+                        s_list[wv], s);
+    if (shared) {
         if (lane == 0)
             for (int k = 0; k < 6; ++k)
                 part[k][wv] = s[k];
@@ -231,10 +260,7 @@ __global__ __launch_bounds__(WP == 1 ? 256 : 64 * WP) void k_particle_integrals(
     } else if (lane != 0) {
         return;
     }
-    for (int k = 0; k < 3; ++k) {
-        Iu[(size_t)k * np + p] = h3 * s[k];
-        Ir[(size_t)k * np + p] = h3 * s[3 + k];
-    }
+    write(p, s);
 }
 
 // Partial FP64 sums of each component over contiguous chunks, one chunk per
@@ -319,7 +345,7 @@ void launch_integrals(ibmx_plan p, const T *u, const double *xp, const double *r
     const int np = p->np;
     hipStream_t s = p->stream;
     if (np >= 4096)
-        hipLaunchKernelGGL((k_particle_integrals<T, 1, O32>), dim3((np + 3) / 4), dim3(256), 0, s,
+        hipLaunchKernelGGL((k_particle_integrals<T, 1, O32>), dim3((np + 3) / 4 + np), dim3(256), 0, s,
                            p->g, np, xp, radius, u, Iu, Ir, alpha_out);
     else if (np >= 512)
         hipLaunchKernelGGL((k_particle_integrals<T, 4, O32>), dim3(np), dim3(256), 0, s, p->g, np,

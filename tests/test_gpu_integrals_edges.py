@@ -1,5 +1,6 @@
 """Particle integrals at the edges of their inputs: field values that must not
-count, particles that are nowhere, boxes longer than 16 bits."""
+count, particles that are nowhere, boxes longer than 16 bits, wide spheres
+among many."""
 import numpy as np
 import pytest
 
@@ -129,3 +130,23 @@ def test_boxes_longer_than_16_bits(n):
                       params=dict(synth.default_params(), disable_mode=0))
     for got, want in zip(_integrals(case, u), _plain_integrals(n, x, 40000.0, u)):
         assert rel_err(got[:, 0], want) <= 1e-12
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+@pytest.mark.parametrize("count", [4096, 4101])
+def test_wide_spheres_among_many(count, precision):
+    """Spheres about the width (40 cells) from which a workgroup takes one,
+    several of a group of four, across seams, the last ones: against the
+    oracle as everywhere (FP64 sums in another order, 1e-12; an FP32 field
+    holds what the oracle reads)."""
+    n = (150, 80, 160)
+    rng = np.random.default_rng(count)
+    x, R = rng.random((3, count)) * np.array(n)[:, None], rng.uniform(0.6, 2.5, count)
+    R[[0, 1, 3, 5, 10]] = 36.4, 19.9, 30.0, np.nextafter(20.0, 30.0), 20.0
+    R[count - 2:] = 25.0, 21.0
+    x[:, 0], x[:, 3] = (3.2, 19.0, 70.0), (140.1, 79.7, 2.5)
+    case = _spheres(n, x, R)
+    u = case.u0.astype(np.float32).astype(np.float64)
+    ref = oracle.particle_integrals(case, u=u)
+    for k, got in zip(("Iu", "Ir"), _integrals(case, u, precision)):
+        assert rel_err(got, ref[k]) <= 1e-12, k
