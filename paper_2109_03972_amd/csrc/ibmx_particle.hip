@@ -26,8 +26,9 @@ __device__ __forceinline__ double root(double s)
 
 // Volume fraction of the cell whose lowest corner is c0 (relative to the
 // particle centre) in a sphere of radius R: the signed corner distances
-// phi_m = |x_m - x_p| - R give alpha = sum -phi_m H(-phi_m) / sum |phi_m|.
-__device__ __forceinline__ double cell_alpha(const double *c0, double h, double R)
+// phi_m = |x_m - x_p| - R give alpha = sum -phi_m H(-phi_m) / sum |phi_m|; any:
+// whether a corner is inside (alpha > 0).
+__device__ __forceinline__ double cell_alpha(const double *c0, double h, double R, bool &any)
 {
     double sq[3][2];
     for (int a = 0; a < 3; ++a) {
@@ -43,8 +44,15 @@ __device__ __forceinline__ double cell_alpha(const double *c0, double h, double 
         num += fmax(-phi, 0.0);
         den += fabs(phi);
     }
+    any = num > 0.0;
     return den > 0.0 ? num / den : 0.0;
 }
+
+// Rows' steps a lane sums over before it adds them to its total: the inside
+// cells' sums drift with the velocity's mean, and a chain of all of a lane's
+// cells (some 110 in a sphere of 24 cells taken by one wave) rounds at the size
+// of its total each time.
+constexpr int kFlush = 16;
 
 // Wave pw of nw's share of one particle's sums, in every lane: s[0..2] of alpha
 // u, s[3..5] of alpha r x u.  A wave takes whole x rows of the particle's
@@ -60,7 +68,8 @@ __device__ __forceinline__ void sphere_sums(const GridC &g, int np, int p, int p
                                             const double *__restrict__ xp,
                                             const double *__restrict__ radius,
                                             const T *__restrict__ u, T *__restrict__ alpha_out,
-                                            int (*list)[2 * IBMX_WAVE], double *s)
+                                            int (*list)[2 * IBMX_WAVE],
+                                            double (*inner)[IBMX_WAVE], double *s)
 {
     const int lane = threadIdx.x & (IBMX_WAVE - 1);
     const double h = g.h, half_diag = 0.5 * sqrt(3.0) * h;
@@ -90,8 +99,10 @@ __device__ __forceinline__ void sphere_sums(const GridC &g, int np, int p, int p
     const double r_in = R - half_diag, r_out = R + half_diag;
     const double r_in2 = r_in > 0.0 ? r_in * r_in : -1.0, r_out2 = r_out * r_out;
     const T *const ub[3] = {u, u + g.nodes, u + 2 * g.nodes};
-    for (int k = 0; k < 6; ++k)
+    for (int k = 0; k < 6; ++k) {
         s[k] = 0.0;
+        inner[k][lane] = 0.0;
+    }
     // lowest corner of cell i along axis a, relative to the centre, and its node
     auto corner = [&](int a, int i) { return g.origin[a] + (lo[a] + i) * h - x[a]; };
     auto node = [&](int a, int i) {
@@ -115,26 +126,28 @@ __device__ __forceinline__ void sphere_sums(const GridC &g, int np, int p, int p
             const unsigned gi =
                 (node(2, i[2]) * (unsigned)g.n[1] + node(1, i[1])) * (unsigned)g.n[0] + node(0, i[0]);
             // the cell's velocity is in flight during the square roots
-            const double uc[3] = {value(0, gi), value(1, gi), value(2, gi)};
+            double uc[3] = {value(0, gi), value(1, gi), value(2, gi)};
             double c0[3], r[3];
             for (int a = 0; a < 3; ++a) {
                 c0[a] = corner(a, i[a]);
                 r[a] = c0[a] + 0.5 * h;
             }
-            const double alpha = cell_alpha(c0, h, R);
+            bool any;
+            const double alpha = cell_alpha(c0, h, R, any);
             // a listed cell may still have all its corners outside: whatever the
-            // field holds there (0 * inf) stays out
-            if (alpha != 0.0) {
-                const double w[3] = {alpha * uc[0], alpha * uc[1], alpha * uc[2]};
-                s[0] += w[0];
-                s[1] += w[1];
-                s[2] += w[2];
-                s[3] += r[1] * w[2] - r[2] * w[1];
-                s[4] += r[2] * w[0] - r[0] * w[2];
-                s[5] += r[0] * w[1] - r[1] * w[0];
-                if (alpha_out)
-                    atomicAdd(&alpha_out[gi], (T)alpha);
-            }
+            // field holds there (0 * inf) stays out (selected while the division
+            // is under way: a branch on alpha cost 4 %)
+            for (int a = 0; a < 3; ++a)
+                uc[a] = any ? uc[a] : 0.0;
+            const double w[3] = {alpha * uc[0], alpha * uc[1], alpha * uc[2]};
+            s[0] += w[0];
+            s[1] += w[1];
+            s[2] += w[2];
+            s[3] += r[1] * w[2] - r[2] * w[1];
+            s[4] += r[2] * w[0] - r[0] * w[2];
+            s[5] += r[0] * w[1] - r[1] * w[0];
+            if (alpha_out && any)
+                atomicAdd(&alpha_out[gi], (T)alpha);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -154,6 +167,15 @@ __device__ __forceinline__ void sphere_sums(const GridC &g, int np, int p, int p
         // sums over the lane's inside cells: of u, and of the parts of r x u
         // that change along them (r_x is the lane's own)
         double v[3] = {0.0, 0.0, 0.0}, m[3] = {0.0, 0.0, 0.0};
+        auto flush = [&]() {
+            const double add[6] = {v[0], v[1], v[2], m[0], m[1] - rx * v[2], rx * v[1] - m[2]};
+#pragma unroll
+            for (int k = 0; k < 6; ++k)
+                inner[k][lane] += add[k];
+            for (int a = 0; a < 3; ++a)
+                v[a] = m[a] = 0.0;
+        };
+        int steps = 0;
         for (int r0 = pw * rpi; r0 < rows; r0 += step) {
             const double ry = corner(1, iy) + 0.5 * h, rz = corner(2, iz) + 0.5 * h;
             const double dc2 = rx2 + ry * ry + rz * rz;
@@ -184,6 +206,10 @@ __device__ __forceinline__ void sphere_sums(const GridC &g, int np, int p, int p
                 listed -= IBMX_WAVE;
                 take(listed, IBMX_WAVE);
             }
+            if (++steps == kFlush) {
+                flush();
+                steps = 0;
+            }
             iy += sy;
             iz += sz;
             if (iy >= ext[1]) {
@@ -191,18 +217,13 @@ __device__ __forceinline__ void sphere_sums(const GridC &g, int np, int p, int p
                 ++iz;
             }
         }
-        s[0] += v[0];
-        s[1] += v[1];
-        s[2] += v[2];
-        s[3] += m[0];
-        s[4] += m[1] - rx * v[2];
-        s[5] += rx * v[1] - m[2];
+        flush();
     }
     if (listed > 0)
         take(0, listed);
 #pragma unroll
     for (int k = 0; k < 6; ++k)
-        s[k] = wave_sum(s[k]);
+        s[k] = wave_sum(s[k] + inner[k][lane]);
 }
 
 // The integrals of every particle: WP waves each, or (WP = 1) a wave each, four
@@ -211,8 +232,8 @@ __device__ __forceinline__ void sphere_sums(const GridC &g, int np, int p, int p
 // others return at once (5000 spheres with one of 100 cells: 2.3 ms, with one
 // wave for it 8.5, with 256 threads for every particle 3.9; looking through the
 // four spheres inside one workgroup cost the bed below another 10 to 20 us in
-// registers).  FP64 sums: per lane in a fixed order, per wave by a fixed shuffle
-// tree, over the waves in wave order.
+// registers).  FP64 sums: per lane in a fixed order, over lanes and waves by fixed
+// trees.
 // Bound by FP64 instructions: the 20,000 spheres of a 512^3 bed, FP32 field,
 // 311 us against 641 with a thread per cell of the box (divisions for the
 // cell's indices, and every wave that met the surface ran the corners for
@@ -226,6 +247,7 @@ __global__ __launch_bounds__(WP == 1 ? 256 : 64 * WP) void k_particle_integrals(
 {
     constexpr int NW = WP == 1 ? 4 : WP;             // waves per workgroup
     __shared__ int s_list[NW][3][2 * IBMX_WAVE];
+    __shared__ double s_inner[NW][6][IBMX_WAVE];
     __shared__ double part[6][NW];
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / IBMX_WAVE);
     const int lane = threadIdx.x & (IBMX_WAVE - 1);
@@ -244,23 +266,23 @@ __global__ __launch_bounds__(WP == 1 ? 256 : 64 * WP) void k_particle_integrals(
         return;
     double s[6];
     sphere_sums<T, O32>(g, np, p, shared ? wv : 0, shared ? NW : 1, xp, radius, u, alpha_out,
-                        s_list[wv], s);
+                        s_list[wv], s_inner[wv], s);
     if (shared) {
         if (lane == 0)
             for (int k = 0; k < 6; ++k)
                 part[k][wv] = s[k];
         __syncthreads();
-        if (threadIdx.x != 0)
+        if (wv != 0)
             return;
         for (int k = 0; k < 6; ++k) {
-            s[k] = part[k][0];
-            for (int w = 1; w < NW; ++w)
-                s[k] += part[k][w];
+            s[k] = part[k][lane % NW];
+#pragma unroll
+            for (int d = NW / 2; d > 0; d >>= 1)
+                s[k] += __shfl_xor(s[k], d, NW);
         }
-    } else if (lane != 0) {
-        return;
     }
-    write(p, s);
+    if (lane == 0)
+        write(p, s);
 }
 
 // Partial FP64 sums of each component over contiguous chunks, one chunk per

@@ -1,6 +1,6 @@
 """Particle integrals at the edges of their inputs: field values that must not
 count, particles that are nowhere, boxes longer than 16 bits, wide spheres
-among many."""
+among many; and the rounding of the sums."""
 import numpy as np
 import pytest
 
@@ -150,3 +150,42 @@ def test_wide_spheres_among_many(count, precision):
     ref = oracle.particle_integrals(case, u=u)
     for k, got in zip(("Iu", "Ir"), _integrals(case, u, precision)):
         assert rel_err(got, ref[k]) <= 1e-12, k
+
+
+@pytest.mark.parametrize("count,R,which,bound", [(240, (8.0, 12.0), 0, 0.82),
+                                                 (4100, (12.0, 12.0), 1, 0.143)])
+def test_rounding_of_the_sums(count, R, which, bound):
+    """RMS error over 150 spheres against 80-bit sums, in units of 2^-53 of the
+    sum of the terms' sizes.  An addition rounds by 0.43 units of its result (rms
+    over the results' mantissas), so a tree over 16 waves of 64 lanes by sqrt(2)
+    of that, 0.61 of the sum, where adding the waves in turn takes 1.0: sixteen
+    waves per sphere, Iu, bound 0.82.  One wave per sphere, Ir: a lane's 113
+    inside cells in one chain drift with the mean velocity, 0.2; in blocks of 16
+    0.06, and 0.04 from the surface cells: bound 0.143."""
+    L = np.longdouble
+    n = (96, 96, 96)
+    rng = np.random.default_rng(count)
+    x, rad = rng.random((3, count)) * 96.0, rng.uniform(*R, count)
+    u = rng.uniform(1.2, 1.4, (3, 96, 96, 96))
+    case = _spheres(n, x, rad, periodic=(1, 1, 1))
+    got = _integrals(case, u)[which]
+    err = []
+    for p in range(150):
+        lo = np.floor(x[:, p] - rad[p]).astype(int)
+        ax = [np.arange(lo[a], int(np.floor(x[a, p] + rad[p])) + 1) for a in range(3)]
+        i = [(ax[a] - x[a, p].astype(L)).reshape([-1 if b == 2 - a else 1 for b in range(3)])
+             for a in range(3)]
+        num = den = L(0)
+        for m in range(8):
+            phi = np.sqrt((i[0] + (m & 1)) ** 2 + (i[1] + (m >> 1 & 1)) ** 2 +
+                          (i[2] + (m >> 2)) ** 2) - L(rad[p])
+            num, den = num + np.maximum(-phi, 0), den + np.abs(phi)
+        w = num / den * u[(slice(None), *np.ix_(ax[2] % 96, ax[1] % 96, ax[0] % 96))]
+        r = [v + L(0.5) for v in i]
+        terms = w if which == 0 else np.stack([r[1] * w[2] - r[2] * w[1],
+                                               r[2] * w[0] - r[0] * w[2],
+                                               r[0] * w[1] - r[1] * w[0]])
+        err.append((got[:, p] - terms.sum((1, 2, 3))) / np.abs(terms).sum((1, 2, 3)))
+    rms = float(np.sqrt(np.mean(np.square(err)))) * 2.0 ** 53
+    print(f"{count} {rms:.3f}", flush=True)
+    assert rms <= bound
