@@ -227,7 +227,7 @@ __device__ __forceinline__ void sphere_sums(const GridC &g, int np, int p, int p
 }
 
 // The integrals of every particle: WP waves each, or (WP = 1) a wave each, four
-// to a workgroup; spheres wider than kShareWidth cells then get a workgroup of
+// to a workgroup; spheres wider than `width` cells then get a workgroup of
 // their own, from a second range of workgroups, one per particle, of which the
 // others return at once (5000 spheres with one of 100 cells: 2.3 ms, with one
 // wave for it 8.5, with 256 threads for every particle 3.9; looking through the
@@ -235,15 +235,14 @@ __device__ __forceinline__ void sphere_sums(const GridC &g, int np, int p, int p
 // registers).  FP64 sums: per lane in a fixed order, over lanes and waves by fixed
 // trees.
 // Bound by FP64 instructions: the 20,000 spheres of a 512^3 bed, FP32 field,
-// 311 us against 641 with a thread per cell of the box (divisions for the
+// 307 us against 641 with a thread per cell of the box (divisions for the
 // cell's indices, and every wave that met the surface ran the corners for
 // all); four waves a particle there take 349 (part-filled lists).
-constexpr double kShareWidth = 40.0;
 template <typename T, int WP, bool O32>
 __global__ __launch_bounds__(WP == 1 ? 256 : 64 * WP) void k_particle_integrals(
-    GridC g, int np, const double *__restrict__ xp, const double *__restrict__ radius,
-    const T *__restrict__ u, double *__restrict__ Iu, double *__restrict__ Ir,
-    T *__restrict__ alpha_out)
+    GridC g, int np, double width, const double *__restrict__ xp,
+    const double *__restrict__ radius, const T *__restrict__ u, double *__restrict__ Iu,
+    double *__restrict__ Ir, T *__restrict__ alpha_out)
 {
     constexpr int NW = WP == 1 ? 4 : WP;             // waves per workgroup
     __shared__ int s_list[NW][3][2 * IBMX_WAVE];
@@ -262,7 +261,7 @@ __global__ __launch_bounds__(WP == 1 ? 256 : 64 * WP) void k_particle_integrals(
     const int nb = WP == 1 ? (np + NW - 1) / NW : 0;
     const bool shared = (int)blockIdx.x >= nb;
     const int p = __builtin_amdgcn_readfirstlane(shared ? blockIdx.x - nb : blockIdx.x * NW + wv);
-    if (WP == 1 && (p >= np || (2.0 * radius[p] > kShareWidth * g.h) != shared))
+    if (WP == 1 && (p >= np || (2.0 * radius[p] > width * g.h) != shared))
         return;
     double s[6];
     sphere_sums<T, O32>(g, np, p, shared ? wv : 0, shared ? NW : 1, xp, radius, u, alpha_out,
@@ -357,24 +356,31 @@ __global__ void k_fill_grid(T *__restrict__ p, long long n)
         p[i] = T(0);
 }
 
-// Waves per particle: one where the particles alone fill the chip (four waves
-// per SIMD), more where they do not.  32-bit field offsets while a component
-// spans less than 4 GB.
+// Waves per particle.  Sixteen up to one particle per CU (256 spheres of 24
+// cells 26 us, with four waves 49; from the next on workgroups queue: 384 of 8
+// cells 15 against 12.5).  Four up to 1535 (1500 of 24 cells 118 us, with one
+// wave 198; of 4 cells both 12).  Above, one for small spheres, whose rows four
+// waves share badly, and four for the ones wider than 10 cells (2000 of 4 cells
+// 12.5 us, with four waves 13.9, of 12 cells 41 with one and 34 with four), from
+// 4096 on only for the ones wider than 40, one wave each filling the chip
+// (20,000 of 8 to 24 cells 313 us, 353 with 10).  32-bit field offsets while a
+// component spans less than 4 GB.
 template <typename T, bool O32>
 void launch_integrals(ibmx_plan p, const T *u, const double *xp, const double *radius, double *Iu,
                       double *Ir, T *alpha_out)
 {
     const int np = p->np;
+    const double width = np >= 4096 ? 40.0 : 10.0;
     hipStream_t s = p->stream;
-    if (np >= 4096)
-        hipLaunchKernelGGL((k_particle_integrals<T, 1, O32>), dim3((np + 3) / 4 + np), dim3(256), 0, s,
-                           p->g, np, xp, radius, u, Iu, Ir, alpha_out);
-    else if (np >= 512)
+    if (np >= 1536)
+        hipLaunchKernelGGL((k_particle_integrals<T, 1, O32>), dim3((np + 3) / 4 + np), dim3(256),
+                           0, s, p->g, np, width, xp, radius, u, Iu, Ir, alpha_out);
+    else if (np > 256)
         hipLaunchKernelGGL((k_particle_integrals<T, 4, O32>), dim3(np), dim3(256), 0, s, p->g, np,
-                           xp, radius, u, Iu, Ir, alpha_out);
+                           width, xp, radius, u, Iu, Ir, alpha_out);
     else
         hipLaunchKernelGGL((k_particle_integrals<T, 16, O32>), dim3(np), dim3(1024), 0, s, p->g,
-                           np, xp, radius, u, Iu, Ir, alpha_out);
+                           np, width, xp, radius, u, Iu, Ir, alpha_out);
 }
 
 template <typename T>

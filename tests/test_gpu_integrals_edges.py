@@ -133,16 +133,18 @@ def test_boxes_longer_than_16_bits(n):
 
 
 @pytest.mark.parametrize("precision", ["f64", "f32"])
-@pytest.mark.parametrize("count", [4096, 4101])
+@pytest.mark.parametrize("count", [256, 257, 1535, 1536, 4095, 4096, 4101])
 def test_wide_spheres_among_many(count, precision):
-    """Spheres about the width (40 cells) from which a workgroup takes one,
-    several of a group of four, across seams, the last ones: against the
+    """Spheres about the widths (10 and 40 cells) from which a workgroup takes
+    one, several of a group of four, across seams, the last ones, in every split
+    of particles over waves: against the
     oracle as everywhere (FP64 sums in another order, 1e-12; an FP32 field
     holds what the oracle reads)."""
     n = (150, 80, 160)
     rng = np.random.default_rng(count)
     x, R = rng.random((3, count)) * np.array(n)[:, None], rng.uniform(0.6, 2.5, count)
     R[[0, 1, 3, 5, 10]] = 36.4, 19.9, 30.0, np.nextafter(20.0, 30.0), 20.0
+    R[[20, 21, 22]] = 5.0, np.nextafter(5.0, 6.0), 7.0
     R[count - 2:] = 25.0, 21.0
     x[:, 0], x[:, 3] = (3.2, 19.0, 70.0), (140.1, 79.7, 2.5)
     case = _spheres(n, x, R)
