@@ -638,9 +638,10 @@ __global__ __launch_bounds__(C == 16 ? 1024 : 256) void k_zsolve(
     const double ih2 = 1.0 / (F.h * F.h), a = s1 * ih2;
     const double e = s0 + s1 * (lam(i, F.n[0], F.h) + lam(j, F.n[1], F.h));
     const double q = e - 2.0 * a;
-    // eps = r + 1/r - 2, dl = 1 - r = 2 eps / (eps + sqrt(eps (eps + 4)))
+    // eps = r + 1/r - 2, dl = 1 - r = 2 eps / (eps + sqrt(eps (eps + 4))); r is
+    // 0 next to 1 long before eps leaves the range
     const double eps = -e / a;
-    double dl = a == 0.0 ? 1.0 : 2.0 * eps / (eps + sqrt(eps) * sqrt(eps + 4.0));
+    double dl = a == 0.0 || eps > 1e30 ? 1.0 : 2.0 * eps / (eps + sqrt(eps) * sqrt(eps + 4.0));
     double s = (1.0 + (1.0 - dl) * (1.0 - dl)) / q;
     const bool singular_block = KIND != kZDirichlet && s0 == 0.0 && blockIdx.x == 0;
     const bool singular = singular_block && col == 0;

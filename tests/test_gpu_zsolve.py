@@ -71,3 +71,27 @@ def test_viscous_columns(nz, wall, nu):
     e = rel_err(u.cpu().numpy(), ref)
     plan.close()
     assert e <= 1e-12, e
+
+
+@pytest.mark.parametrize("nz,wall", [(64, 1), (300, 1), (64, 0)])
+@pytest.mark.parametrize("nu", [5e-324, 1e-310, 1e-307, 1e-200])
+def test_vanishing_viscosity(nz, wall, nu):
+    """A viscosity too small to couple the rows: the same bits as without any."""
+    import torch
+    dev = require_gpu()
+    n, per = (8, 8, nz), (1, 1, 0 if wall else 1)
+    case = _case(n, per, seed=3)
+    rng = np.random.default_rng(nz)
+    u0, lap = (torch.as_tensor(rng.normal(size=(3, nz, 8, 8)), device=dev) for _ in range(2))
+    P = torch.zeros((nz, 8, 8), dtype=torch.float64, device=dev)
+    out = []
+    for v in (0.0, nu):
+        case.params = dict(case.params, c=0.8, nu_f=v)
+        plan = ibmx.Plan.from_case(case, "f64")
+        u = u0.clone()
+        plan.fluid_helmholtz(u, lap, P, 0.4)
+        plan.check("helmholtz")
+        plan.close()
+        out.append(u.cpu().numpy())
+    assert np.isfinite(out[0]).all()
+    np.testing.assert_array_equal(*out)
