@@ -549,14 +549,22 @@ __device__ __forceinline__ double lam(int m, int n, double h)
 //   periodic  y_{-1} = F / (1 - r^nz),       x_nz = G / (1 - r^nz),
 //   walls     y_{-1} = (+-B + r^nz F)/(1 - r^2nz),  x_nz = +- s y_{nz-1}/(1 -+ r),
 // F, G the filters' ends from zero (F = sum r^(nz-1-k) d_k, G = sum r^k s y_k)
-// and B = sum r^k d_k.  All r enter as 1 - r = dl, found without
-// cancellation: low modes have r close to 1, and y -> y - dl y keeps their
-// rounding at the level of the elimination's.
+// and B = sum r^k d_k.
+//
+// Rounding: low modes have r close to 1, so above 1/4 r is held as 1 - r = dl,
+// found without cancellation, and enters a filter step as hi + lo, hi the nearest
+// number to 1 - dl: y_k = fma(hi, y, fma(lo, y, d)), one rounding at the size of
+// y.  Each filter runs twice over a chunk, from zero for the chunk's end and then
+// from the true value before it, so that a row takes one filter rounding and not
+// another for the carry, and s comes from two-term sums.  RMS error of a column of
+// 64 rows, in units of 2^-53 of the solution (emulated; s1/h^2 = -0.0013, -0.13,
+// -4, -30, lambda_xy h^2 = 0, -0.15, -4, -8): 0.8 to 1.1, at -30 and 0 2.0; the
+// elimination 0.8 to 1.6, at -30 and 0 5.4; the pressure 0.7 to 1.1 and 0.8 to 4.5.
 //
 // A workgroup holds 8 neighbouring modes (128 B runs in memory) and their
-// whole columns in registers, C rows per thread, 8 chunks of rows per wave;
-// the filters run within the chunks, the chunk ends are combined by a wave
-// scan and over the waves through LDS.  Rows are padded in front (chunk 0).
+// whole columns in registers, C rows per thread, 8 chunks of rows per wave; the
+// chunk ends are combined by a wave scan and over the waves through LDS.  Rows
+// are padded in front (chunk 0).
 // What bounds it is memory: 16 B read and 16 B written per mode value, once,
 // where the elimination and substitution read and write it twice (and a
 // periodic z takes a forward FFT, a division and an inverse FFT: three times).
@@ -576,24 +584,33 @@ __device__ __forceinline__ double2 operator*(double a, double2 b)
 {
     return make_double2(a * b.x, a * b.y);
 }
-// d + r v with r = 1 - dl
-__device__ __forceinline__ double2 z_step(double2 d, double2 v, double dl)
-{
-    return make_double2(fma(-dl, v.x, v.x + d.x), fma(-dl, v.y, v.y + d.y));
-}
-// r^m r^n = (1 - a)(1 - b) -> 1 - that
-__device__ __forceinline__ double z_mul(double a, double b) { return a + b - a * b; }
-// 1 - (1 - dl)^n
-__device__ __forceinline__ double z_pow(double dl, int n)
-{
-    double r = 0.0;
-    for (; n > 0; n >>= 1) {
-        if (n & 1)
-            r = z_mul(r, dl);
-        dl = dl * (2.0 - dl);
+
+// Powers of a mode's r, held as p itself (near = 0) or as 1 - p (near = 1, r
+// above 1/4).
+struct ZRoot {
+    double near, sign;   // sign = 1 - 2 near
+    __device__ explicit ZRoot(bool n) : near(n ? 1.0 : 0.0), sign(n ? -1.0 : 1.0) {}
+    __device__ double one() const { return 1.0 - near; }                    // of r^0
+    __device__ double val(double p) const { return fma(sign, p, near); }    // the power
+    __device__ double rest(double p) const { return fma(-sign, p, 1.0 - near); }   // 1 - it
+    __device__ double mul(double a, double b) const { return fma(sign * a, b, near * (a + b)); }
+    __device__ double pow(double p, int n) const
+    {
+        double r = one();
+        for (; n > 0; n >>= 1) {
+            if (n & 1)
+                r = mul(r, p);
+            p = mul(p, p);
+        }
+        return r;
     }
-    return r;
-}
+    // d + v times the power
+    __device__ double2 step(double2 d, double2 v, double p) const
+    {
+        const double hi = val(p), lo = near * ((1.0 - hi) - p);
+        return make_double2(fma(hi, v.x, fma(lo, v.x, d.x)), fma(hi, v.y, fma(lo, v.y, d.y)));
+    }
+};
 __device__ __forceinline__ double2 z_shfl_up(double2 v, int d)
 {
     return make_double2(__shfl_up(v.x, d, IBMX_WAVE), __shfl_up(v.y, d, IBMX_WAVE));
@@ -611,6 +628,13 @@ __device__ __forceinline__ double2 z_wave_sum(double2 v)
         v.y += __shfl_xor(v.y, d, IBMX_WAVE);
     }
     return v;
+}
+// a + b = hi + lo exactly (no order of sizes needed)
+__device__ __forceinline__ void two_sum(double a, double b, double &hi, double &lo)
+{
+    hi = a + b;
+    const double t = hi - a;
+    lo = (a - (hi - t)) + (b - t);
 }
 
 // KIND: the closure; the system with s0 = 0 and a zero-gradient or periodic
@@ -636,18 +660,35 @@ __global__ __launch_bounds__(C == 16 ? 1024 : 256) void k_zsolve(
         v[r] = col < nxy && k0 + r >= 0 ? Z[(size_t)(k0 + r) * nxy + col] : make_double2(0.0, 0.0);
     const int i = col >> logny, j = col & ((1 << logny) - 1);
     const double ih2 = 1.0 / (F.h * F.h), a = s1 * ih2;
-    const double e = s0 + s1 * (lam(i, F.n[0], F.h) + lam(j, F.n[1], F.h));
-    const double q = e - 2.0 * a;
-    // eps = r + 1/r - 2, dl = 1 - r = 2 eps / (eps + sqrt(eps (eps + 4))); r is
-    // 0 next to 1 long before eps leaves the range
+    const double lx = lam(i, F.n[0], F.h), ly = lam(j, F.n[1], F.h);
+    const double e = s0 + s1 * (lx + ly);
+    // eps = r + 1/r - 2; r = 2 / (eps + 2 + w), 1 - r = 2 eps / (eps + w) with w =
+    // sqrt(eps (eps + 4)); r is 0 next to 1 long before eps leaves the range
     const double eps = -e / a;
-    double dl = a == 0.0 || eps > 1e30 ? 1.0 : 2.0 * eps / (eps + sqrt(eps) * sqrt(eps + 4.0));
-    double s = (1.0 + (1.0 - dl) * (1.0 - dl)) / q;
     const bool singular_block = KIND != kZDirichlet && s0 == 0.0 && blockIdx.x == 0;
     const bool singular = singular_block && col == 0;
+    const ZRoot root(singular || eps < 2.0);
+    double p1, s;
     if (singular) {
-        dl = 0.0;
+        p1 = 0.0;
         s = -1.0 / a;
+    } else {
+        const double w = sqrt(eps) * sqrt(eps + 4.0);
+        p1 = a == 0.0 || eps > 1e30 ? 0.0 : eps < 2.0 ? 2.0 * eps / (eps + w)
+                                                       : 2.0 / (eps + 2.0 + w);
+        // s = (1 + r^2) / (e - 2 a), numerator and denominator to two terms
+        double lh, ll, eh, el, qh, ql, nh, nl;
+        two_sum(lx, ly, lh, ll);
+        const double t = s1 * lh;
+        two_sum(s0, t, eh, el);
+        el += fma(s1, lh, -t) + s1 * ll;
+        two_sum(eh, -2.0 * a, qh, ql);
+        ql += el;
+        const double r = root.val(p1), r2 = r * r;
+        two_sum(1.0, r2, nh, nl);
+        nl += fma(r, r, -r2);
+        s = nh / qh;
+        s += (fma(-s, qh, nh) + (nl - s * ql)) / qh;
     }
     // the mean over the rows of one value per thread and row (for the
     // singular mode; every thread of the block calls it)
@@ -672,117 +713,117 @@ __global__ __launch_bounds__(C == 16 ? 1024 : 256) void k_zsolve(
         if (singular)
 #pragma unroll
             for (int r = 0; r < C; ++r)
-                v[r] = v[r] + (-1.0) * m;
+                v[r] = k0 + r >= 0 ? v[r] + (-1.0) * m : v[r];
     };
     if (KIND == kZPeriodic && singular_block)
         take_mean();
     // powers of r over a chunk, 2, 4 and 8 chunks, and over the whole column
-    double dC = dl;
+    double pC = p1;
 #pragma unroll
     for (int c = 1; c < C; c <<= 1)
-        dC = dC * (2.0 - dC);
-    const double d2 = dC * (2.0 - dC), d4 = d2 * (2.0 - d2), d8 = d4 * (2.0 - d4);
-    const double dn = z_pow(dl, nz), dks = z_pow(dl, ks);
+        pC = root.mul(pC, pC);
+    const double p2 = root.mul(pC, pC), p4 = root.mul(p2, p2), p8 = root.mul(p4, p4);
+    const double pn = root.pow(p1, nz), pks = root.pow(p1, ks);
     auto chunks_pow = [&](int n) {   // n < 8 chunks
-        double p = (n & 1) ? dC : 0.0;
+        double p = (n & 1) ? pC : root.one();
         if (n & 2)
-            p = z_mul(p, d2);
+            p = root.mul(p, p2);
         if (n & 4)
-            p = z_mul(p, d4);
+            p = root.mul(p, p4);
         return p;
     };
-    // up: the chunk's filter from zero, its end, and with walls the chunk's
-    // share of B
+    const double2 zero = make_double2(0.0, 0.0);
+    // up: the chunk's end from zero, and with walls the chunk's share of B
+    double2 E = zero;
+#pragma unroll
+    for (int r = 0; r < C; ++r)
+        E = root.step(v[r], E, p1);   // rows before row 0 hold zeros
     if (KIND != kZPeriodic) {
-        double2 b = make_double2(0.0, 0.0);
+        double2 b = zero;
 #pragma unroll
         for (int r = C - 1; r >= 0; --r)
             if (k0 + r >= 0)
-                b = z_step(v[r], b, dl);
-        b = z_wave_sum((1.0 - dks) * b);
+                b = root.step(v[r], b, p1);
+        b = z_wave_sum(root.val(pks) * b);
         if (ci == 0)
             w_sum[wv][mode] = b;
     }
-#pragma unroll
-    for (int r = 1; r < C; ++r)
-        v[r] = z_step(v[r], v[r - 1], dl);
-    double2 E = v[C - 1];
     {
         double2 t = z_shfl_up(E, kZModes);
         if (ci >= 1)
-            E = z_step(E, t, dC);
+            E = root.step(E, t, pC);
         t = z_shfl_up(E, 2 * kZModes);
         if (ci >= 2)
-            E = z_step(E, t, d2);
+            E = root.step(E, t, p2);
         t = z_shfl_up(E, 4 * kZModes);
         if (ci >= 4)
-            E = z_step(E, t, d4);
+            E = root.step(E, t, p4);
     }
     if (ci == kZChunks - 1)
         w_end[wv][mode] = E;
     __syncthreads();
-    double2 cw = make_double2(0.0, 0.0), Fe = cw, B = cw;
+    double2 cw = zero, Fe = cw, B = cw;
     for (int w = 0; w < nw; ++w) {
         if (w == wv)
             cw = Fe;
-        Fe = z_step(w_end[w][mode], Fe, d8);
+        Fe = root.step(w_end[w][mode], Fe, p8);
         if (KIND != kZPeriodic)
             B = B + w_sum[w][mode];
     }
-    // y before row 0, and before the chunk
-    double2 Y0 = make_double2(0.0, 0.0), X0 = Y0;
+    // y before row 0
+    double2 Y0 = zero, X0 = Y0;
     if (!singular) {
         if (KIND == kZPeriodic) {
-            Y0 = (1.0 / dn) * Fe;
+            Y0 = (1.0 / root.rest(pn)) * Fe;
         } else {
-            Y0 = (1.0 / (dn * (2.0 - dn))) * ((double)KIND * B + (1.0 - dn) * Fe);
-            const double2 ye = Fe + (1.0 - dn) * Y0;
-            X0 = ((double)KIND * s / (KIND == kZNeumann ? dl : 2.0 - dl)) * ye;
+            const double rn = root.val(pn), r = root.val(p1);
+            Y0 = (1.0 / (root.rest(pn) * (1.0 + rn))) * ((double)KIND * B + rn * Fe);
+            const double2 ye = Fe + rn * Y0;
+            X0 = ((double)KIND * s / (KIND == kZNeumann ? root.rest(p1) : 1.0 + r)) * ye;
         }
     }
+    // y of every row from the value before the chunk, times s
     {
         double2 c = z_shfl_up(E, kZModes);
         if (ci == 0)
-            c = make_double2(0.0, 0.0);
-        c = c + (1.0 - chunks_pow(ci)) * cw + (1.0 - dks) * Y0;
+            c = zero;
+        c = c + root.val(chunks_pow(ci)) * cw + root.val(pks) * Y0;
 #pragma unroll
         for (int r = 0; r < C; ++r)
             if (k0 + r >= 0) {
-                c = make_double2(fma(-dl, c.x, c.x), fma(-dl, c.y, c.y));
-                v[r] = v[r] + c;
+                c = root.step(v[r], c, p1);
+                v[r] = s * c;
             }
     }
     if (singular_block) {
         if (KIND == kZPeriodic) {
             take_mean();
         } else if (singular && k0 + C == nz) {
-            v[C - 1] = make_double2(0.0, 0.0);   // the top value is pinned to 0
+            v[C - 1] = zero;   // the top value is pinned to 0
         }
     }
     // down: the same from the top
     {
-        double2 g = make_double2(0.0, 0.0);
+        double2 g = zero;
 #pragma unroll
         for (int r = C - 1; r >= 0; --r)
-            if (k0 + r >= 0) {
-                g = z_step(s * v[r], g, dl);
-                v[r] = g;
-            }
+            if (k0 + r >= 0)
+                g = root.step(v[r], g, p1);
         if (KIND == kZPeriodic) {
-            const double2 t = z_wave_sum((1.0 - dks) * g);
+            const double2 t = z_wave_sum(root.val(pks) * g);
             if (ci == 0)
                 w_sum[wv][mode] = t;
         }
         E = g;
         double2 t = z_shfl_down(E, kZModes);
         if (ci < kZChunks - 1)
-            E = z_step(E, t, dC);
+            E = root.step(E, t, pC);
         t = z_shfl_down(E, 2 * kZModes);
         if (ci < kZChunks - 2)
-            E = z_step(E, t, d2);
+            E = root.step(E, t, p2);
         t = z_shfl_down(E, 4 * kZModes);
         if (ci < kZChunks - 4)
-            E = z_step(E, t, d4);
+            E = root.step(E, t, p4);
     }
     __syncthreads();
     if (ci == 0)
@@ -792,19 +833,19 @@ __global__ __launch_bounds__(C == 16 ? 1024 : 256) void k_zsolve(
         double2 G = w_sum[0][mode];
         for (int w = 1; w < nw; ++w)
             G = G + w_sum[w][mode];
-        X0 = (1.0 / dn) * G;
+        X0 = (1.0 / root.rest(pn)) * G;
     }
     for (int w = nw - 1; w > wv; --w)
-        X0 = z_step(w_end[w][mode], X0, d8);
+        X0 = root.step(w_end[w][mode], X0, p8);
     {
         double2 c = z_shfl_down(E, kZModes);
         if (ci == kZChunks - 1)
-            c = make_double2(0.0, 0.0);
-        c = c + (1.0 - chunks_pow(kZChunks - 1 - ci)) * X0;
+            c = zero;
+        c = c + root.val(chunks_pow(kZChunks - 1 - ci)) * X0;
 #pragma unroll
         for (int r = C - 1; r >= 0; --r) {
-            c = make_double2(fma(-dl, c.x, c.x), fma(-dl, c.y, c.y));
-            v[r] = v[r] + c;
+            c = root.step(v[r], c, p1);
+            v[r] = c;
         }
     }
     if (singular_block)
