@@ -176,15 +176,19 @@ dim3 column_grid(const FluidC &F)
     return dim3((F.n[0] + PX - 1) / PX, (F.n[1] + PY - 1) / PY, (F.n[2] + F.planes - 1) / F.planes);
 }
 
-// Planes per run: 32 (a run re-reads two planes), fewer while that leaves less
-// than eight workgroups per CU, down to 4.  On 128^3, FP64, 32 planes are one
-// workgroup per CU: predictor 80 us, correction 55, against 70 and 45 with 4
-// (the face divergence, 33, does not care); on 512^3 16, 32 and 64 take the same.
-int column_planes(const int *n)
+// Planes per run: 32 (a run re-reads two planes), fewer, down to 4, while that
+// leaves fewer workgroups than `want`: 2048 for FP64 fields, 600 for FP32, whose
+// rings take half the LDS, so that a CU holds twice as many.  Predictor: FP64, 96^3
+// 51 us with 32 planes, 34 with 4; 256 x 256 x 128 254 with 32 (1024 workgroups),
+// 225 with 16.  FP32, 128^3 59 with 32, 42 with 8; 256 x 256 x 128 130 with 32, 136
+// with 16; 150 x 133 x 177 73 with 32 (612 workgroups), 76 with 16.  On 512^3 16, 32
+// and 64 take the same.
+int column_planes(const int *n, size_t value_bytes)
 {
+    const long long want = value_bytes == 8 ? 2048 : 600;
     const long long cols = (long long)((n[0] + PX - 1) / PX) * ((n[1] + PY - 1) / PY);
     int planes = 32;
-    while (planes > 4 && cols * ((n[2] + planes - 1) / planes) < 2048)
+    while (planes > 4 && cols * ((n[2] + planes - 1) / planes) < want)
         planes /= 2;
     return planes;
 }
@@ -1236,7 +1240,7 @@ FluidC fluid_constants(const ibmx_plan p, double theta)
         F.n[a] = g.n[a];
         F.periodic[a] = g.periodic[a];
     }
-    F.planes = column_planes(F.n);
+    F.planes = column_planes(F.n, p->prec == IBMX_F64 ? sizeof(double) : sizeof(float));
     F.h = g.h;
     F.ih = 1.0 / g.h;
     F.ih2 = 1.0 / (g.h * g.h);
