@@ -219,7 +219,8 @@ IBMX_API ibmx_status ibmx_plan_reserve(ibmx_plan plan, int32_t pair_cap, int32_t
                                        int32_t cell_cap, int32_t flags);
 
 /* Change the parameters (n_iter may not exceed the value the plan was
- * created with). */
+ * created with).  Tiles that neither ibmx_plan_set_tiles nor ibmx_tune chose
+ * become the default ones of the new delta. */
 IBMX_API ibmx_status ibmx_plan_set_params(ibmx_plan plan, const ibmx_params *params);
 
 /* Change the stream used by later calls. */

@@ -232,6 +232,8 @@ extern "C" ibmx_status ibmx_tune(ibmx_plan p, void *u, void *f_tot, const double
     ibmx_status st2 = ibmx_plan_alloc_tiles(p, best[0], best[1], best[2]);
     if (st2 != IBMX_OK)
         st2 = ibmx_plan_alloc_tiles(p, orig[0], orig[1], orig[2]);
+    if (best_ms < FLT_MAX)
+        p->tiles_default = 0;
     (void)ibmx_plan_set_launch(p, best_block, best_persist);
     if (pending != 0)
         (void)hipMemcpy(p->d_err, &pending, sizeof(int), hipMemcpyHostToDevice);

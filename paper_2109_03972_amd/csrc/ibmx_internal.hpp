@@ -47,6 +47,7 @@ struct ibmx_plan_s {
     // tiles
     TileC tc;
     long long tile_cap;   // tiles the tile arrays are sized for
+    int tiles_default;    // 1: the shape is the default one (follows the delta)
     int *tile_count;      // [ntiles + 1]
     int *tile_start;      // [ntiles + 1]
     int *tile_cursor;     // [ntiles]
@@ -151,6 +152,7 @@ struct ProfScope {
 
 ibmx_status ibmx_launch_check();
 ibmx_status ibmx_plan_alloc_tiles(ibmx_plan p, int tx, int ty, int tz);
+ibmx_status ibmx_plan_default_tiles(ibmx_plan p);
 ibmx_status ibmx_spread_allow_lds(ibmx_plan p);
 void ibmx_plan_drop_graph(ibmx_plan p);
 ibmx_status ibmx_plan_scan_reserve(ibmx_plan p, long long n);

@@ -218,22 +218,34 @@ ibmx_status check_params(const ibmx_grid *g, const ibmx_params *prm)
         free_plan(p);
         return st;
     }
-    // default tiles: 16 x 16 x 8 nodes; FP64 with the four-point delta 16 x 8 x 8:
-    // the interpolation's region of the larger tile, 19 x 19 x 11 nodes, takes
-    // 95 KB of LDS and leaves one workgroup per CU, that of 19 x 11 x 11 nodes
-    // 55 KB and two.  FP64, four-point: 128^3 with 200 spheres 396 -> 370 us,
-    // 256 x 256 x 512 with 2000 7.57 -> 7.32 ms, 71 x 69 x 254 with 17 249 ->
-    // 189 us.  The three-point one (78 KB, two workgroups) loses by the larger
-    // halo: 247 -> 262 us and 4.29 -> 5.09 ms on the first two.
     st = ibmx_plan_scan_reserve(p, np);
+    // the tile arrays serve both default shapes, so that a change of the delta
+    // allocates nothing
+    if (st == IBMX_OK && p->prec == IBMX_F64)
+        st = ibmx_plan_alloc_tiles(p, 16, 8, 8);
     if (st == IBMX_OK)
-        st = ibmx_plan_alloc_tiles(p, 16, p->prec == IBMX_F64 && p->prm.kernel == 4 ? 8 : 16, 8);
+        st = ibmx_plan_alloc_tiles(p, 16, 16, 8);
+    if (st == IBMX_OK)
+        st = ibmx_plan_default_tiles(p);
     if (st != IBMX_OK) {
         free_plan(p);
         return st;
     }
     *out = p;
     return IBMX_OK;
+}
+
+// Default tiles: 16 x 16 x 8 nodes; FP64 with the four-point delta 16 x 8 x 8:
+// the interpolation's region of the larger tile, 19 x 19 x 11 nodes, takes
+// 95 KB of LDS and leaves one workgroup per CU, that of 19 x 11 x 11 nodes
+// 55 KB and two.  FP64, four-point: 128^3 with 200 spheres 396 -> 370 us,
+// 256 x 256 x 512 with 2000 7.57 -> 7.32 ms, 71 x 69 x 254 with 17 249 ->
+// 189 us.  The three-point one (78 KB, two workgroups) loses by the larger
+// halo: 247 -> 262 us and 4.29 -> 5.09 ms on the first two.
+ibmx_status ibmx_plan_default_tiles(ibmx_plan p)
+{
+    p->tiles_default = 1;
+    return ibmx_plan_alloc_tiles(p, 16, p->prec == IBMX_F64 && p->prm.kernel == 4 ? 8 : 16, 8);
 }
 
 ibmx_status ibmx_plan_alloc_tiles(ibmx_plan p, int tx, int ty, int tz)
@@ -379,7 +391,7 @@ extern "C" ibmx_status ibmx_plan_set_params(ibmx_plan p, const ibmx_params *prm)
         return st;
     }
     ibmx_plan_drop_graph(p);
-    return IBMX_OK;
+    return p->tiles_default && p->prm.kernel != old.kernel ? ibmx_plan_default_tiles(p) : IBMX_OK;
 }
 
 extern "C" ibmx_status ibmx_plan_set_tiles(ibmx_plan p, int32_t tx, int32_t ty, int32_t tz)
@@ -392,6 +404,8 @@ extern "C" ibmx_status ibmx_plan_set_tiles(ibmx_plan p, int32_t tx, int32_t ty, 
     const ibmx_status st = ibmx_plan_alloc_tiles(p, tx, ty, tz);
     if (st != IBMX_OK)
         (void)ibmx_plan_alloc_tiles(p, old[0], old[1], old[2]);
+    else
+        p->tiles_default = 0;
     return st;
 }
 
