@@ -372,8 +372,8 @@ IBMX_API ibmx_status ibmx_pairs(ibmx_plan plan, const double *xp, const double *
  * ibmx_forcing through a HIP graph (the batching form of the loop: one graph
  * launch per call).  The first call, and any call whose pointer arguments
  * differ from the captured ones or that follows a change of the plan's
- * parameters, tiles or markers, captures ibmx_forcing's launches
- * into a graph kept by the plan (on a private capture stream, so the plan's
+ * parameters, tiles or markers or a growth of its workspace, captures
+ * ibmx_forcing's launches into a graph kept by the plan (on a private capture stream, so the plan's
  * stream may be the default stream); every call then launches that graph on
  * the plan's stream.  Same arguments, results and deferred errors as
  * ibmx_forcing.  With profiling on, the whole call is timed as IBMX_K_GRAPH.

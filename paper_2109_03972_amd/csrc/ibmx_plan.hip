@@ -340,11 +340,13 @@ ibmx_status ibmx_plan_alloc_tiles(ibmx_plan p, int tx, int ty, int tz)
     return ibmx_spread_allow_lds(p);
 }
 
-// Grow the scan workspace to serve scans of up to n elements.
+// Grow the scan workspace to serve scans of up to n elements (a captured
+// forcing call holds its address).
 ibmx_status ibmx_plan_scan_reserve(ibmx_plan p, long long n)
 {
     if (p->scan_aux && p->scan_cap >= n)
         return IBMX_OK;
+    ibmx_plan_drop_graph(p);
     if (p->scan_aux)
         (void)hipFree(p->scan_aux);
     p->scan_aux = nullptr;
