@@ -259,8 +259,9 @@ __global__ __launch_bounds__(256) void k_pairs_count(PairC P, int np, const doub
 
 // The lists: a wave per particle orders its kept partners by id (each lane
 // counts the smaller ones) and writes them with their gaps, then its walls; a
-// particle with more partners than were kept searches again.  The first wave
-// also writes the totals.
+// particle with more partners than were kept searches again.  Where the list is
+// too short it holds the first entries in (i, j) order.  The first wave also
+// writes the totals.
 __global__ __launch_bounds__(256) void k_pairs_emit(PairC P, int np, const double *xp,
                                                     const double *radius, const int *cell_start,
                                                     const int *cellp, const int *found,
@@ -302,20 +303,32 @@ __global__ __launch_bounds__(256) void k_pairs_emit(PairC P, int np, const doubl
             pairs_out[cap + pos] = j;
             gap_out[pos] = gap_to(j);
         }
-    } else if (cnt > kKept) {
+    } else if (cnt > kKept && base < cap) {
         // searched again, in candidate order into the scratch half of pairs_out,
-        // then sorted and completed by lane 0
+        // then sorted and completed by lane 0; where the list's end cuts the
+        // particle's partners, those of the smallest ids: up to `last`, found by
+        // bisection (for one particle of a call at most)
+        const int n = min(cnt, cap - base);
+        int last = np - 1, below = i;
+        while (n < cnt && below + 1 < last) {
+            const int mid = below + (last - below) / 2;
+            int c = 0;
+            search_partners(P, np, xp, radius, cell_start, cellp, i, xi, Ri, [&](bool hit, int j) {
+                c += __popcll(__ballot(hit && j <= mid));
+            });
+            (c >= n ? last : below) = mid;
+        }
         int at = 0;
         search_partners(P, np, xp, radius, cell_start, cellp, i, xi, Ri, [&](bool hit, int j) {
+            hit = hit && j <= last;
             const unsigned long long m = __ballot(hit);
             const int pos = base + at + __popcll(m & ((1ULL << lane) - 1ULL));
-            if (hit && pos < cap)
+            if (hit)
                 pairs_out[cap + pos] = j;
             at += __popcll(m);
         });
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-        const int n = min(cnt, cap - base);
-        if (n > 0 && lane == 0) {
+        if (lane == 0) {
             sort_segment(pairs_out + cap + base, n);
             for (int k = 0; k < n; ++k) {
                 pairs_out[base + k] = i;

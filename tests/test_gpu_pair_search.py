@@ -5,6 +5,7 @@ and forces against the oracle as everywhere in the pair pass."""
 import numpy as np
 import pytest
 
+import oracle
 from paper_2109_03972_amd import synth
 from tests.test_gpu_pairs import _check, _gpu_pairs
 
@@ -54,3 +55,33 @@ def test_edges_seams_and_walls(periodic, rmax):
         # one cell per axis: a large sphere that touches none but widens the bound
         case.radius[0], case.xp[:, 0] = 15.0, 21.0
     _check(case, _gpu_pairs(case))
+
+
+@pytest.mark.parametrize("around", [20, 32, 33, 64, 150])
+@pytest.mark.parametrize("short", [1, 7, 19])
+def test_short_lists_hold_the_first_pairs(around, short):
+    """A capacity that cuts the list within one particle's partners: the entries
+    that fit are the first of the canonical order, whichever way the partners
+    were found."""
+    import torch
+    from paper_2109_03972_amd import ibmx
+    from tests._util import dev_case
+    p = synth.spiral_points(around).T * (8.0 + 1.2)
+    rng = np.random.default_rng(around)
+    x = np.concatenate([[[24.0], [20.0], [22.0]], p + np.array([[24.0], [20.0], [22.0]])], 1)
+    x[:, 1:] = x[:, 1 + rng.permutation(around)]
+    case = _spheres(x, [8.0] + [1.0] * around, (1, 1, 1))
+    case.u0 = None
+    ref = oracle.pairs(case)
+    D = dev_case(case, "f64")
+    plan = ibmx.Plan.from_case(case, "f64")
+    plan.set_markers(D["body"], D["dV"])
+    for cap in (around - short, around - 1, around):
+        res = plan.pairs(D["xp"], D["radius"], D["mass"], D["up"], D["wp"], pair_cap=cap)
+        over = cap < ref["pairs"].shape[1]
+        assert plan.status() == (ibmx.ECAPACITY if over else ibmx.OK)
+        assert int(res["counts"][0]) == ref["pairs"].shape[1]
+        k = min(cap, ref["pairs"].shape[1])
+        np.testing.assert_array_equal(res["pairs"][:, :k].cpu().numpy(), ref["pairs"][:, :k])
+        np.testing.assert_allclose(res["gap"][:k].cpu().numpy(), ref["gap"][:k], rtol=0, atol=1e-12)
+    plan.close()
