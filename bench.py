@@ -113,20 +113,17 @@ def kernel_sources_hash() -> str:
 
 
 def fluid_bytes(kind: str, s: int, nodes: int, walls_z: bool = True) -> float:
-    """Bytes one fluid call must move (s = bytes of the field type; the
-    solves work in FP64 on the half spectrum of nx/2 + 1 complex modes per
-    row, about 8 B per node, and on an FP64 real grid, 8 B per node).
+    """Bytes of one fluid call in its textbook form (s = bytes of the field type;
+    the solves work in FP64 on the half spectrum of nx/2 + 1 complex modes per
+    row, about 8 B per node, and on an FP64 real grid, 8 B per node): a rate by
+    these compares with other solvers, not with the memory (fluid_moved does).
 
     spectrum (one solve between the x passes): the y pass forward and back
            (read and write 8 each: 16 + 16), and across walls an elimination
            (read and write the spectrum twice: 32) or along a periodic z two
-           more passes and the division (48).  This is the count of the
-           textbook forms, kept so that rates stay comparable; where the
-           solve along z runs as one pass it moves 16, so a rate by these
-           bytes can lie above what the memory moves.
+           more passes and the division (48).
     predictor: reads u, N (3s each) and P (s); writes u~, N and nu L u (3s each).
-    project: face values and divergence (reads 3s, writes 3s + 8; the
-           library writes u_f there only on the rims of its columns), the
+    project: face values and divergence (reads 3s, writes 3s + 8), the
            forward x pass from the real grid (read 8, write 8), the spectrum,
            the inverse x pass into the real grid (16), the correction (reads
            the solution, u, u_f, P; writes u, u_f, P: 8 + 14s; phi is not
@@ -146,6 +143,39 @@ def fluid_bytes(kind: str, s: int, nodes: int, walls_z: bool = True) -> float:
     else:
         raise KeyError(kind)
     return float(per) * nodes
+
+
+def fluid_moved(kind: str, s: int, n, walls_z: bool = True) -> float:
+    """Bytes the library's kernels move for one fluid call, each array of each
+    kernel once: fluid_bytes less what the library saves.  The solve along z
+    reads and writes the spectrum once (16) where the filters take it (columns
+    of at most 2048 rows, between walls at least 16; otherwise the elimination,
+    32), and u_f* passes through memory only where a face leaves its
+    workgroup's 64 x 4 x 32 cells; the correction forms the rest again."""
+    nodes = float(n[0]) * n[1] * n[2]
+    if kind == "predictor":
+        return fluid_bytes(kind, s, 1) * nodes
+    one_pass = n[2] <= 2048 and (n[2] >= 16 or not walls_z)
+    spectrum = 16 + 16 + (16 if one_pass else 32 if walls_z else 48)
+    rim = s * (1.0 / 64 + 1.0 / 4 + 1.0 / 32)
+    if kind == "project":
+        per = (3 * s + 8 + rim) + 16 + spectrum + 16 + (8 + 11 * s + rim)
+    elif kind == "helmholtz":
+        per = 3 * ((2 * s + 8) + spectrum + (8 + s))
+    else:
+        raise KeyError(kind)
+    return per * nodes
+
+
+def fluid_roofline(kind: str, case, ms: float) -> dict:
+    """The FP32 call's rate by the bytes its kernels move, as a fraction of the
+    memory's peak, and by the textbook form's bytes."""
+    walls = not case.periodic[2]
+    moved = fluid_moved(kind, 4, case.n, walls)
+    textbook = fluid_bytes(kind, 4, int(case.n[0]) * int(case.n[1]) * int(case.n[2]), walls)
+    rate = moved / (ms * 1e-3) / 1e9
+    return dict(bytes=moved, achieved_GBs=round(rate, 1), frac=round(rate / HBM_PEAK_GBS, 4),
+                textbook_GBs=round(textbook / (ms * 1e-3) / 1e9, 1))
 
 
 def measured_traffic(workload: str, kind: str, tile) -> "float | None":
@@ -504,19 +534,14 @@ def main():
         fluid_stage=dict(predictor_ms=r32["extras"]["predictor_ms"],
                          helmholtz_ms=r32["extras"]["helmholtz_ms"],
                          project_ms=r32["extras"]["project_ms"],
-                         roofline={k: dict(
-                             bytes=fluid_bytes(k, 4, nodes, not case.periodic[2]),
-                             achieved_GBs=round(fluid_bytes(k, 4, nodes, not case.periodic[2])
-                                                / (r32["extras"][k + "_ms"] * 1e-3) / 1e9, 1),
-                             frac=round(fluid_bytes(k, 4, nodes, not case.periodic[2])
-                                        / (r32["extras"][k + "_ms"] * 1e-3) / 1e9
-                                        / HBM_PEAK_GBS, 4))
-                             for k in ("predictor", "helmholtz", "project")},
+                         roofline={k: fluid_roofline(k, case, r32["extras"][k + "_ms"])
+                                   for k in ("predictor", "helmholtz", "project")},
                          note="the collocated solver's other steps of one Runge-Kutta stage on "
                               "the workload's grid (FP32 fields): ibmx_fluid_predictor, "
                               "ibmx_fluid_helmholtz and ibmx_project (FP64 FFT/tridiagonal "
-                              "solves); bytes of the textbook solves, of which the one-pass "
-                              "solve along z moves 16 per node less; not part of the step"),
+                              "solves); bytes and frac by what the kernels move, "
+                              "textbook_GBs by the textbook solves' bytes; not part of the "
+                              "step"),
         substeps=dict(ms=r32["extras"]["substeps_ms"], n_sub=r32["extras"]["substeps_n_sub"],
                       particles=case.np_, cpu_oracle_ms=cpu_sub_ms,
                       note="ibmx_particle_substeps of one time step (Hertz/ACTM contacts, "
