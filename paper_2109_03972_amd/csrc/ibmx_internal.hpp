@@ -66,9 +66,9 @@ struct ibmx_plan_s {
     int block;            // threads per workgroup of the forcing passes
     int persist;          // 1: passes as a persistent grid looping over tiles
 
-    // backward workspace (allocated by the first backward call): replay
-    // grid T[3][nodes], per-pass amplitude and Jacobian T4[n_iter][3][nm],
-    // per-marker cotangent sums double4[2][nm]
+    // backward workspace (ibmx_plan_reserve): replay grid T[3][nodes], per-pass
+    // amplitude and Jacobian T4[n_iter][3][nm], the pass-independent part
+    // double4[nm] and the cotangent sums double2[3][nm] of every marker
     void *bw_u;
     size_t bw_bytes;
 
@@ -102,9 +102,9 @@ struct ibmx_plan_s {
     double *s_buf;        // [s_cap] sub-step records, stage forces, entries, constants
     long long s_cap;
 
-    // fluid-solve workspace (first ibmx_project / ibmx_fluid_helmholtz call)
+    // fluid-solve workspace (ibmx_plan_reserve)
     double *fl_r;         // real right-hand side / solution [nodes]
-    double2 *fl_z;        // half spectrum [nz][ny][nx/2 + 1]
+    double2 *fl_z;        // half spectrum [nz][nx/2 + 1][ny], y fastest
     double2 *fl_tw[3];
 
     // last-call statistics

@@ -698,7 +698,7 @@ extern "C" ibmx_status ibmx_pairs(ibmx_plan p, const double *xp, const double *r
                        pair_gap, (const int *)p->p_woff, wall_cap, walls_out, wall_gap, counts_out,
                        p->d_err);
     // forces: previous history aligned with the new lists, per-particle
-    // adjacency, then one thread per particle
+    // adjacency, then a group of lanes per particle
     const ContactLists C{pair_cap, wall_cap, pairs_out, walls_out, counts_out};
     const Hist hold{p->c_hist, p->c_hist + (size_t)kHist * pair_cap};
     {
