@@ -47,3 +47,42 @@ def test_particle_sums_splits(np_, marks, n_iter):
         e = rel_err(got.cpu().numpy(), ref[k])
         assert e <= 1e-12, (k, e)
     plan.close()
+
+
+@pytest.mark.parametrize("np_,d", [(200, 28.0), (600, 28.0), (4200, 10.0)])
+def test_rounding_of_the_particle_sums(np_, d):
+    """RMS error of S over 150 spheres against 80-bit sums, in units of 2^-53 of
+    the sum.  With u = 0 and one pass every marker's amplitude is known to the
+    bit, and all have one sign.  An addition rounds by 0.43 units of its result
+    (RMS over the results' mantissas), a tree over the waves' lanes and the waves
+    by sqrt(2) of that, 0.61, the lanes' chains by less than 0.2 on top of it in
+    squares; sixteen waves added in turn take 1.0: bound 0.82."""
+    import torch
+    dev = require_gpu()
+    rng = np.random.default_rng(np_)
+    n = (96, 96, 96)
+    diam = np.full(np_, d)
+    moff, body, dV = synth.build_markers(diam, 1.0, rng)
+    prm = dict(synth.default_params(), disable_mode=0, n_iter=1)
+    plan = ibmx.Plan(n, 1.0, (0.0, 0.0, 0.0), (1, 1, 1), prm, moff, "f64")
+    t = lambda a: torch.as_tensor(np.ascontiguousarray(a), dtype=torch.float64, device=dev)
+    keep = t(body), t(dV)
+    plan.set_markers(*keep)
+    x, up = rng.random((3, np_)) * 96.0, rng.uniform(0.8, 1.2, (3, np_))
+    u = torch.zeros((3, 96, 96, 96), dtype=torch.float64, device=dev)
+    wp = rng.uniform(-0.01, 0.01, (3, np_))
+    S, _ = plan.forcing(u, torch.zeros_like(u), t(x), t(up), t(wp))
+    plan.check("forcing")
+    plan.close()
+    S, err = S.cpu().numpy(), []
+    for p in range(150):
+        o = body[:, moff[p]:moff[p + 1]]
+        w = wp[:, p]
+        r = np.stack([up[0, p] + (w[1] * o[2] - w[2] * o[1]), up[1, p] + (w[2] * o[0] - w[0] * o[2]),
+                      up[2, p] + (w[0] * o[1] - w[1] * o[0])])
+        assert np.all(r > 0.0)
+        G = (r / prm["c"] * dV[p]).astype(np.longdouble)
+        err.append((S[:, p] - G.sum(1)) / G.sum(1))
+    rms = float(np.sqrt(np.mean(np.square(err)))) * 2.0 ** 53
+    print(f"{np_} {rms:.3f}", flush=True)
+    assert rms <= 0.82
