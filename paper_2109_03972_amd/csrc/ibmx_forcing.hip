@@ -1910,12 +1910,18 @@ template <typename T, int NP>
 void launch_sums_few(ibmx_plan p, int want_res, double h3, const typename V4<T>::type *Gm,
                      typename V4<T>::type *Gs, double *S_out, double *T_out)
 {
-    // one wave per particle where the particles fill the chip, else as many
-    // as the average particle's markers take (at most 4, or 16 for fewer than
-    // 512 particles)
+    // Waves per particle, by the average particle's chunks of 64 markers (FP32,
+    // three passes, with the clearing of the counters).  Two chunks: two waves
+    // while a workgroup finds an idle CU, then one (511 particles 12.8 us, with one
+    // wave 13.0; 700 13.3 with one, 13.7 with two, 2000 16.6 and 18.0).  More: four
+    // (7 chunks, 511 particles 16.2 us, with one 17.4, with seven 17.6; 10000 97 and
+    // 105 with one), and while CUs idle eight, as the larger ones of a bed have more
+    // than the average (150 of 8 to 20 cells, whole call: 292 us, with four 295),
+    // or sixteen (79 chunks, 64 particles 22.6 us, with four 29.1; 300 49.7, 50.8).
     const int np = p->np, nm = p->nm;
-    const int chunks = (nm / np + IBMX_WAVE - 1) / IBMX_WAVE, most = np < 512 ? 16 : 4;
-    const int waves = np >= 4096 ? 1 : (chunks < most ? (chunks > 1 ? chunks : 1) : most);
+    const int chunks = (nm / np + IBMX_WAVE - 1) / IBMX_WAVE;
+    const int most = np > 256 ? 4 : chunks > 16 ? 16 : 8;
+    const int waves = chunks > most ? most : chunks == 2 && np >= 700 ? 1 : chunks > 1 ? chunks : 1;
     if (waves == 1)
         hipLaunchKernelGGL((k_particle_sums_few<T, NP, false>), dim3(nblocks(np, 4)), dim3(256), 0,
                            p->stream, np, nm, want_res, h3, (const int *)p->d_moff, p->body,

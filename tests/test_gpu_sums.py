@@ -86,3 +86,12 @@ def test_rounding_of_the_particle_sums(np_, d):
     rms = float(np.sqrt(np.mean(np.square(err)))) * 2.0 ** 53
     print(f"{np_} {rms:.3f}", flush=True)
     assert rms <= 0.82
+
+
+@pytest.mark.parametrize("np_,marks", [(256, (1040, 1100)), (257, (1040, 1100)), (40, (900, 1020)),
+                                       (699, (65, 128)), (700, (65, 128)), (90, (130, 190)),
+                                       (4096, (129, 150)), (5000, (64, 65))])
+def test_particle_sums_at_the_lines(np_, marks):
+    """As above at the lines between the waves per particle: 2, 4 and 16 chunks
+    of 64 markers on average, 256 and 700 particles."""
+    test_particle_sums_splits(np_, marks, 2)
