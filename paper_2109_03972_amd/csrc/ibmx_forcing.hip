@@ -79,7 +79,13 @@ __device__ __forceinline__ int axis_node(const GridC &g, int a, int b, int k)
 }
 
 // Workgroups are dealt to the XCDs round-robin; give each XCD a contiguous
-// range of tiles / marker chunks so that neighbouring tiles share its L2.
+// range of tiles so that neighbouring tiles share its L2.  In x-y-z order that is
+// one z slab per XCD, and workgroups do not move between XCDs: a bed that fills
+// half the height leaves half the chip idle.  Measured against runs of 16 tiles
+// dealt to the XCDs in turn: interpolation / spreading of a pass on the 256 x 256
+// x 512 bed (its markers on four XCDs, the busiest 2.3 times the mean; dealt, 1.04)
+// 153 / 152 us against 84 / 88, on the 512^3 bed (1.65; 1.01) 713 / 741 against
+// 582 / 580, on 64^3 with one sphere 8.7 / 11.2 against 8.8 / 11.5.
 __device__ __forceinline__ int xcd_remap(int bid, int nblocks)
 {
     const int q = nblocks / NXCD, r = nblocks % NXCD;
@@ -2040,9 +2046,10 @@ ibmx_status run_backward(ibmx_plan p, const T *u0, const double *xp, const doubl
     if (!p->bw_u || p->bw_bytes < ibmx_backward_bytes(p))
         return IBMX_ESTATE;
     T *us = (T *)p->bw_u;
-    T4 *GJ = (T4 *)(us + (G3 + 15) / 16 * 16);   // records start on 64 bytes
-    double4 *fst = (double4 *)(GJ + 3 * (size_t)nm * p->n_iter_cap);
-    double2 *acc = (double2 *)(fst + nm);
+    // from 64 bytes on, by falling alignment: double4, T4 (32 or 16 bytes), double2
+    double4 *fst = (double4 *)(us + (G3 + 15) / 16 * 16);
+    T4 *GJ = (T4 *)(fst + nm);
+    double2 *acc = (double2 *)(GJ + 3 * (size_t)nm * p->n_iter_cap);
     bin_markers<T, W>(p, xp, up, wp, mask);
     const int cb = 4096;
     {
@@ -2147,8 +2154,8 @@ hipError_t allow_lds_w(int bytes_interp, int bytes_spread)
 
 }  // namespace
 
-// Adjoint workspace: the replay grid T[3][nodes], per-pass amplitude and
-// Jacobian T4[n_iter][3][nm], the pass-independent double4[nm] and the
+// Adjoint workspace: the replay grid T[3][nodes], the pass-independent
+// double4[nm], per-pass amplitude and Jacobian T4[n_iter][3][nm] and the
 // double2[3][nm] sums of every marker.
 size_t ibmx_backward_bytes(ibmx_plan p)
 {
