@@ -310,23 +310,22 @@ __global__ __launch_bounds__(256) void k_pairs_emit(PairC P, int np, const doubl
         // bisection (for one particle of a call at most)
         const int n = min(cnt, cap - base);
         int last = np - 1, below = i;
-        while (n < cnt && below + 1 < last) {
-            const int mid = below + (last - below) / 2;
-            int c = 0;
+#pragma unroll 1
+        for (bool probe = true; probe;) {
+            probe = n < cnt && below + 1 < last;
+            const int upto = probe ? below + (last - below) / 2 : last;
+            int at = 0;
             search_partners(P, np, xp, radius, cell_start, cellp, i, xi, Ri, [&](bool hit, int j) {
-                c += __popcll(__ballot(hit && j <= mid));
+                hit = hit && j <= upto;
+                const unsigned long long m = __ballot(hit);
+                const int pos = base + at + __popcll(m & ((1ULL << lane) - 1ULL));
+                if (hit && !probe)
+                    pairs_out[cap + pos] = j;
+                at += __popcll(m);
             });
-            (c >= n ? last : below) = mid;
+            if (probe)
+                (at >= n ? last : below) = upto;
         }
-        int at = 0;
-        search_partners(P, np, xp, radius, cell_start, cellp, i, xi, Ri, [&](bool hit, int j) {
-            hit = hit && j <= last;
-            const unsigned long long m = __ballot(hit);
-            const int pos = base + at + __popcll(m & ((1ULL << lane) - 1ULL));
-            if (hit)
-                pairs_out[cap + pos] = j;
-            at += __popcll(m);
-        });
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
         if (lane == 0) {
             sort_segment(pairs_out + cap + base, n);
