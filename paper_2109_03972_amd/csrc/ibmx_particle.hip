@@ -48,10 +48,11 @@ __device__ __forceinline__ double cell_alpha(const double *c0, double h, double 
     return den > 0.0 ? num / den : 0.0;
 }
 
-// Rows' steps a lane sums over before it adds them to its total: the inside
-// cells' sums drift with the velocity's mean, and a chain of all of a lane's
-// cells (some 110 in a sphere of 24 cells taken by one wave) rounds at the size
-// of its total each time.
+// Rows' steps a lane sums over before it adds them to its total (BLOCKS): the
+// inside cells' sums drift with the velocity's mean, and a chain of all of a
+// lane's cells (some 110 in a sphere of 24 cells taken by one wave) rounds at the
+// size of its total each time.  With sixteen waves a chain is shorter than a block
+// (24 cells: 7), or that much shorter than with fewer.
 constexpr int kFlush = 16;
 
 // Wave pw of nw's share of one particle's sums, in every lane: s[0..2] of alpha
@@ -63,7 +64,7 @@ constexpr int kFlush = 16;
 // between (a third of the box) need eight corner distances: they are collected
 // in the wave's LDS list (their box indices) and taken 64 at a time, so that no
 // lane idles through the square roots of another's cell.
-template <typename T, bool O32>
+template <typename T, bool O32, bool BLOCKS>
 __device__ __forceinline__ void sphere_sums(const GridC &g, int np, int p, int pw, int nw,
                                             const double *__restrict__ xp,
                                             const double *__restrict__ radius,
@@ -101,7 +102,8 @@ __device__ __forceinline__ void sphere_sums(const GridC &g, int np, int p, int p
     const T *const ub[3] = {u, u + g.nodes, u + 2 * g.nodes};
     for (int k = 0; k < 6; ++k) {
         s[k] = 0.0;
-        inner[k][lane] = 0.0;
+        if (BLOCKS)
+            inner[k][lane] = 0.0;
     }
     // lowest corner of cell i along axis a, relative to the centre, and its node
     auto corner = [&](int a, int i) { return g.origin[a] + (lo[a] + i) * h - x[a]; };
@@ -171,7 +173,10 @@ __device__ __forceinline__ void sphere_sums(const GridC &g, int np, int p, int p
             const double add[6] = {v[0], v[1], v[2], m[0], m[1] - rx * v[2], rx * v[1] - m[2]};
 #pragma unroll
             for (int k = 0; k < 6; ++k)
-                inner[k][lane] += add[k];
+                if (BLOCKS)
+                    inner[k][lane] += add[k];
+                else
+                    s[k] += add[k];
             for (int a = 0; a < 3; ++a)
                 v[a] = m[a] = 0.0;
         };
@@ -206,7 +211,7 @@ __device__ __forceinline__ void sphere_sums(const GridC &g, int np, int p, int p
                 listed -= IBMX_WAVE;
                 take(listed, IBMX_WAVE);
             }
-            if (++steps == kFlush) {
+            if (BLOCKS && ++steps == kFlush) {
                 flush();
                 steps = 0;
             }
@@ -223,7 +228,7 @@ __device__ __forceinline__ void sphere_sums(const GridC &g, int np, int p, int p
         take(0, listed);
 #pragma unroll
     for (int k = 0; k < 6; ++k)
-        s[k] = wave_sum(s[k] + inner[k][lane]);
+        s[k] = wave_sum(BLOCKS ? s[k] + inner[k][lane] : s[k]);
 }
 
 // The integrals of every particle: WP waves each, or (WP = 1) a wave each, four
@@ -246,7 +251,7 @@ __global__ __launch_bounds__(WP == 1 ? 256 : 64 * WP) void k_particle_integrals(
 {
     constexpr int NW = WP == 1 ? 4 : WP;             // waves per workgroup
     __shared__ int s_list[NW][3][2 * IBMX_WAVE];
-    __shared__ double s_inner[NW][6][IBMX_WAVE];
+    __shared__ double s_inner[WP < 16 ? NW : 1][6][IBMX_WAVE];
     __shared__ double part[6][NW];
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / IBMX_WAVE);
     const int lane = threadIdx.x & (IBMX_WAVE - 1);
@@ -264,8 +269,8 @@ __global__ __launch_bounds__(WP == 1 ? 256 : 64 * WP) void k_particle_integrals(
     if (WP == 1 && (p >= np || (2.0 * radius[p] > width * g.h) != shared))
         return;
     double s[6];
-    sphere_sums<T, O32>(g, np, p, shared ? wv : 0, shared ? NW : 1, xp, radius, u, alpha_out,
-                        s_list[wv], s_inner[wv], s);
+    sphere_sums<T, O32, (WP < 16)>(g, np, p, shared ? wv : 0, shared ? NW : 1, xp, radius, u,
+                                   alpha_out, s_list[wv], s_inner[WP < 16 ? wv : 0], s);
     if (shared) {
         if (lane == 0)
             for (int k = 0; k < 6; ++k)
