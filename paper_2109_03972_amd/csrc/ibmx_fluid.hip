@@ -678,8 +678,9 @@ __global__ __launch_bounds__(C == 16 ? 1024 : 256) void k_zsolve(
         s = -1.0 / a;
     } else {
         const double w = sqrt(eps) * sqrt(eps + 4.0);
-        p1 = a == 0.0 || eps > 1e30 ? 0.0 : eps < 2.0 ? 2.0 * eps / (eps + w)
-                                                       : 2.0 / (eps + 2.0 + w);
+        const bool near = eps < 2.0;
+        p1 = a == 0.0 || eps > 1e30 ? 0.0
+                                    : (near ? 2.0 * eps : 2.0) / (eps + (near ? 0.0 : 2.0) + w);
         // s = (1 + r^2) / (e - 2 a), numerator and denominator to two terms
         double lh, ll, eh, el, qh, ql, nh, nl;
         two_sum(lx, ly, lh, ll);
@@ -691,8 +692,9 @@ __global__ __launch_bounds__(C == 16 ? 1024 : 256) void k_zsolve(
         const double r = root.val(p1), r2 = r * r;
         two_sum(1.0, r2, nh, nl);
         nl += fma(r, r, -r2);
-        s = nh / qh;
-        s += (fma(-s, qh, nh) + (nl - s * ql)) / qh;
+        const double iq = 1.0 / qh;
+        s = nh * iq;
+        s += (fma(-s, qh, nh) + (nl - s * ql)) * iq;
     }
     // the mean over the rows of one value per thread and row (for the
     // singular mode; every thread of the block calls it)
