@@ -572,8 +572,8 @@ __device__ __forceinline__ double lam(int m, int n, double h)
 // What bounds it is memory: 16 B read and 16 B written per mode value, once,
 // where the elimination and substitution read and write it twice (and a
 // periodic z takes a forward FFT, a division and an inverse FFT: three times).
-// On 512^3 with walls 483 us a solve (2.16 GB, 4.5 TB/s, the copy rate)
-// against 946; on 128^3 periodic 17 us against 53.
+// On 512^3 with walls 478 us a solve (2.16 GB and 0.25 GB of spilled registers, 4.5
+// TB/s and 5.0, the copy rate) against 946; on 128^3 periodic 18 us against 53.
 // ---------------------------------------------------------------------------
 constexpr int kZModes = 8;                            // modes per workgroup
 constexpr int kZChunks = IBMX_WAVE / kZModes;         // row chunks per wave

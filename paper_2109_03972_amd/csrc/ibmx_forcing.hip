@@ -1387,7 +1387,7 @@ __global__ __launch_bounds__(256) void k_particle_sums(
 // particles are few: 150 spheres, FP32, three passes 8.4 us against 64 with a
 // wave per particle that loaded pass by pass; the 2000 spheres of the 256 x 256
 // x 512 bed, five passes, 48 against 103; 512^3 bed (bytes: whole lines for
-// scattered 16-byte records) 367 against 410.
+// scattered 16-byte records) 351 against 410.
 constexpr int kFewPasses = 8;
 template <typename T, int NP, bool BLOCK>
 __global__ __launch_bounds__(BLOCK ? 1024 : 256) void k_particle_sums_few(
